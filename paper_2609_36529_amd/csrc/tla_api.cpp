@@ -163,7 +163,7 @@ tla::PrepBufs prep_bufs(const Layout& L, const void* base, bool ninv) {
   char* b = (char*)base;
   return tla::PrepBufs{(float*)(b + L.p_coef), (float*)(b + L.p_gC), (void*)(b + L.p_ops),
                        (ninv && L.p_ninv < L.p_size) ? (float*)(b + L.p_ninv) : nullptr,
-                       ninv ? 1 : 0};
+                       ninv ? 1 : 0, nullptr};
 }
 tla::SavedBufs saved_bufs(const Layout& L, const void* saved) {
   char* b = (char*)saved;
@@ -329,14 +329,19 @@ static int fwd_impl(const tla_desc* d, const int32_t* cu, long long total, const
   const tla::PrepBufs pb =
       saved ? prep_bufs(L, (char*)saved + L.sv_prep, true) : prep_bufs(L, ws, false);
   hipError_t e;
+  // inference with bf16 operands and K >= 64: the look-ahead recurrence
+  const bool la = !saved && tla::la_instance(s.K, s.C, s.E, s.in_bf16);
   if (ntok > 0) {
-    e = timed(PROF_PREP, st, [&] { return tla::launch_prep(s, in, pb, st); });
+    e = timed(PROF_PREP, st, [&] {
+      return la ? tla::launch_prep_la(s, in, pb, st) : tla::launch_prep(s, in, pb, st);
+    });
     if (e != hipSuccess) return device_fail(e, "prep kernel");
   }
   if (ntok > 0 || s_final) {
     tla::SavedBufs sv = saved_bufs(L, saved);
     e = timed(PROF_FWD, st, [&] {
-      return tla::launch_fwd(s, in, pb, o, s_final, saved ? &sv : nullptr, st);
+      return la ? tla::launch_fwd_la(s, in, pb, o, s_final, nullptr, st)
+                : tla::launch_fwd(s, in, pb, o, s_final, saved ? &sv : nullptr, st);
     });
     if (e != hipSuccess) return device_fail(e, "forward kernel");
   }

@@ -1579,32 +1579,10 @@ constexpr bool fwd_dual() {
          sizeof(DualSmem<T, KD, C, E>) <= 160 * 1024;
 }
 
-// The same kernel with two slices per tile (inference at E = 16, K = 128,
-// chunk 64): 8 value columns per workgroup, twice the workgroups.
-template <typename T, int KD, int C, int E>
-constexpr bool fwd_pk() {
-  return sizeof(T) == 2 && E == 16 && KD == 128 && C == 64 &&
-         sizeof(DualSmem<T, KD, C, E, true>) <= 160 * 1024;
-}
-
 template <typename T, int KD, int C, int E>
 static hipError_t fwd_inst(const Shape& s, const FwdIn& in, const PrepBufs& p, void* o,
                            float* s_final, const SavedBufs* sv, hipStream_t st) {
   SavedBufs none{nullptr, nullptr, nullptr};
-  if constexpr (fwd_pk<T, KD, C, E>()) {
-    if (!sv) {
-      const size_t smem = sizeof(DualSmem<T, KD, C, E, true>);
-      static bool attr_pk = false;
-      if (!attr_pk) {
-        (void)hipFuncSetAttribute((const void*)k_fwd_dual<T, KD, C, E, true>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        attr_pk = true;
-      }
-      hipLaunchKernelGGL((k_fwd_dual<T, KD, C, E, true>), dim3(s.NH * (s.V / 8)), dim3(512), smem,
-                         st, s, in, p, o, s_final, none, 0);
-      return hipGetLastError();
-    }
-  }
   if constexpr (fwd_dual<T, KD, C, E>()) {
     const size_t smem = sizeof(DualSmem<T, KD, C, E>);
     static bool attr_set = false;
