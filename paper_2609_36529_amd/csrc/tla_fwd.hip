@@ -25,6 +25,7 @@
 //           the 16-column tiling exact.
 #include "tla_common.hpp"
 #include "tla_internal.hpp"
+#include "tla_la_fwd.hpp"
 
 namespace tla {
 

@@ -1,6 +1,8 @@
 // Look-ahead forward of chunkwise triadic linear attention on gfx950 (bf16
 // operands, K >= 64): the prep kernel with the cross-chunk tiles, and the
 // recurrent forward.  See tla_la.hpp for the algebra.
+// (Compiled as part of tla_fwd.hip.)
+#pragma once
 #include "tla_la.hpp"
 
 namespace tla {
