@@ -331,8 +331,8 @@ __global__ __launch_bounds__(NW * 64) void k_bwd_rec(Shape s, FwdIn in, const vo
     if (w < NT) {
       const int rt = w;
       store_tile16(bb.dU + chs * C * (size_t)V + (size_t)(16 * rt) * V + v0, sm.dUf[rt][l], g, n, V);
-      store_tile16(bb.dW + chs * C * (size_t)V + (size_t)(16 * rt) * V + v0,
-                   s.variant == 1 ? sm.dWs[rt][l] : zero4(), g, n, V);
+      if (s.variant == 1)  // (sGLA: dW = 0, never read)
+        store_tile16(bb.dW + chs * C * (size_t)V + (size_t)(16 * rt) * V + v0, sm.dWs[rt][l], g, n, V);
     }
   };
   RecStage<T, KD, C, E, NTHR> stage;
@@ -656,7 +656,10 @@ struct StateSmem {
 
 // PDS: the chunk-end state gradients arrive as bf16 (hi, lo) tile pairs
 // (see k_bwd_rec) and enter U dS'^T and <S, dS'> with both parts.
-template <typename T, int KD, int C, int E, bool PDS>
+// GDN: without it (sGLA) dW = 0, so Y and da vanish: no dW rows, and three or
+// four of the five or six products a tile (B2 T1999 H16 E4 with PDS: 192 ->
+// 142 us; a run-time branch in one kernel spilled 140 registers).
+template <typename T, int KD, int C, int E, bool PDS, bool GDN>
 __global__ __launch_bounds__(STATE_NTHR) void k_bwd_state(Shape s, FwdIn in, const void* dOv,
                                                           PrepBufs p, SavedBufs sv, BwdBufs bb) {
   constexpr int NT = C / 16;
@@ -699,6 +702,8 @@ __global__ __launch_bounds__(STATE_NTHR) void k_bwd_state(Shape s, FwdIn in, con
     const int n8 = ncols / 8;
     Raw8<T> ro[IT];
     f32x4 rw[IT][2], ru[IT][2];
+#pragma unroll
+    for (int it = 0; it < IT; ++it) rw[it][0] = rw[it][1] = zero4();
     // unconditional loads from clamped positions (masked below), so that
     // every load of the batch is in flight before the first wait
 #pragma unroll
@@ -708,8 +713,10 @@ __global__ __launch_bounds__(STATE_NTHR) void k_bwd_state(Shape s, FwdIn in, con
       ro[it] = load8(dOg + (size_t)min(t0 + r, s.T - 1) * vrs + col);
       const float* pw = dWg + (size_t)r * V + col;
       const float* pu = Ug + (size_t)r * V + col;
-      rw[it][0] = *(const f32x4*)pw;
-      rw[it][1] = *(const f32x4*)(pw + 4);
+      if constexpr (GDN) {
+        rw[it][0] = *(const f32x4*)pw;
+        rw[it][1] = *(const f32x4*)(pw + 4);
+      }
       ru[it][0] = *(const f32x4*)pu;
       ru[it][1] = *(const f32x4*)(pu + 4);
     }
@@ -725,10 +732,12 @@ __global__ __launch_bounds__(STATE_NTHR) void k_bwd_state(Shape s, FwdIn in, con
       if constexpr (SPLIT) {
         *(uint4*)&sm.dO[r][c] = dov.w[0];
         bf16x4 h0, l0, h1, l1;
-        split_frag(w0, h0, l0);
-        split_frag(w1, h1, l1);
-        *(bf16x8*)&sm.dWh[r][c] = __builtin_shufflevector(h0, h1, 0, 1, 2, 3, 4, 5, 6, 7);
-        *(bf16x8*)&sm.dWl[r][c] = __builtin_shufflevector(l0, l1, 0, 1, 2, 3, 4, 5, 6, 7);
+        if constexpr (GDN) {
+          split_frag(w0, h0, l0);
+          split_frag(w1, h1, l1);
+          *(bf16x8*)&sm.dWh[r][c] = __builtin_shufflevector(h0, h1, 0, 1, 2, 3, 4, 5, 6, 7);
+          *(bf16x8*)&sm.dWl[r][c] = __builtin_shufflevector(l0, l1, 0, 1, 2, 3, 4, 5, 6, 7);
+        }
         split_frag(u0, h0, l0);
         split_frag(u1, h1, l1);
         *(bf16x8*)&sm.Uh[r][c] = __builtin_shufflevector(h0, h1, 0, 1, 2, 3, 4, 5, 6, 7);
@@ -869,21 +878,21 @@ __global__ __launch_bounds__(STATE_NTHR) void k_bwd_state(Shape s, FwdIn in, con
           const int r = 16 * (rt0 + i) + n;
           const int cc = col + 8 * g;
           const Raw8<T> ao = *(const Raw8<T>*)&sm.dO[r][cc];
-          const Raw8<T> awh = *(const Raw8<T>*)&sm.dWh[r][cc];
           const Raw8<T> auh = *(const Raw8<T>*)&sm.Uh[r][cc];
-          Raw8<T> awl, aul;
+          Raw8<T> awh, awl, aul;
+          if constexpr (GDN) awh = *(const Raw8<T>*)&sm.dWh[r][cc];
           if constexpr (SPLIT) {
-            awl = *(const Raw8<T>*)&sm.dWl[r][cc];
+            if constexpr (GDN) awl = *(const Raw8<T>*)&sm.dWl[r][cc];
             aul = *(const Raw8<T>*)&sm.Ul[r][cc];
           }
 #pragma unroll
           for (int c = 0; c < CTW; ++c) {
             if (q * CTW + c >= KT) continue;
             mma8(X[i][c], ao, sbuf[c][pp]);
-            mma8(Y[i][c], awh, sbuf[c][pp]);
+            if constexpr (GDN) mma8(Y[i][c], awh, sbuf[c][pp]);
             mma8(Vp[i][c], auh, dbuf[c][pp]);
             if constexpr (SPLIT) {
-              mma8(Y[i][c], awl, sbuf[c][pp]);
+              if constexpr (GDN) mma8(Y[i][c], awl, sbuf[c][pp]);
               mma8(Vp[i][c], aul, dbuf[c][pp]);
             }
             if constexpr (PDS) mma8(Vp[i][c], auh, dlbuf[c][pp]);
@@ -912,11 +921,12 @@ __global__ __launch_bounds__(STATE_NTHR) void k_bwd_state(Shape s, FwdIn in, con
       for (int c = 0; c < CTW; ++c) {
         if (q * CTW + c >= KT) continue;
         dq[i][c] += cb * X[i][c];
-        dk[i][c] += ca * Y[i][c] + cc * Vp[i][c];
+        if constexpr (GDN) dk[i][c] += ca * Y[i][c] + cc * Vp[i][c];
+        else dk[i][c] += cc * Vp[i][c];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           const float kj = unpack(kv[i][c], j), qj = unpack(qv[i][c], j);
-          rs[0][4 * i + j] += kj * Y[i][c][j];   // d a_e
+          if constexpr (GDN) rs[0][4 * i + j] += kj * Y[i][c][j];  // d a_e
           rs[1][4 * i + j] += qj * X[i][c][j];   // d b_e
           rs[2][4 * i + j] += kj * Vp[i][c][j];  // d c_e
         }
@@ -926,7 +936,7 @@ __global__ __launch_bounds__(STATE_NTHR) void k_bwd_state(Shape s, FwdIn in, con
     const int rrow = 16 * (rt0 + (n >> 2)) + 4 * g + (n & 3);
 #pragma unroll
     for (int kind = 0; kind < 3; ++kind) {
-      const float x = group16_transpose_sum(rs[kind], n);
+      const float x = GDN || kind ? group16_transpose_sum(rs[kind], n) : 0.f;
       if (rows && (n >> 2) < RTW) sm.red[par][q][kind][rrow] = x;
     }
     if (w < 4) {
@@ -1842,20 +1852,23 @@ template <typename T, int KD, int C, int E>
 static hipError_t state_inst(const Shape& s, const FwdIn& in, const void* dO, const PrepBufs& p,
                              const SavedBufs& sv, const BwdBufs& bb, hipStream_t st) {
   const size_t smem = sizeof(StateSmem<T, KD, C, E>);
-  auto go = [&](auto pds_c) {
-    constexpr bool PDS = decltype(pds_c)::value;
+  auto go = [&](auto pds_c, auto gdn_c) {
+    constexpr bool PDS = decltype(pds_c)::value, GDN = decltype(gdn_c)::value;
     static bool attr = false;
     if (!attr) {
-      (void)hipFuncSetAttribute((const void*)k_bwd_state<T, KD, C, E, PDS>,
+      (void)hipFuncSetAttribute((const void*)k_bwd_state<T, KD, C, E, PDS, GDN>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
       attr = true;
     }
-    hipLaunchKernelGGL((k_bwd_state<T, KD, C, E, PDS>), dim3(s.NH * s.Nc), dim3(STATE_NTHR), smem,
+    hipLaunchKernelGGL((k_bwd_state<T, KD, C, E, PDS, GDN>), dim3(s.NH * s.Nc), dim3(STATE_NTHR), smem,
                        st, s, in, dO, p, sv, bb);
     return hipGetLastError();
   };
-  if (sizeof(T) == 2 && bb.dSck_lo) return go(std::integral_constant<bool, sizeof(T) == 2>{});
-  return go(std::integral_constant<bool, false>{});
+  auto pick = [&](auto pds_c) {
+    return s.variant == 1 ? go(pds_c, std::true_type{}) : go(pds_c, std::false_type{});
+  };
+  if (sizeof(T) == 2 && bb.dSck_lo) return pick(std::integral_constant<bool, sizeof(T) == 2>{});
+  return pick(std::false_type{});
 }
 
 template <typename T, int KD, int C, int E>
