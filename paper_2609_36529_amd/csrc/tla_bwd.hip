@@ -88,6 +88,9 @@ __device__ __forceinline__ void bmma_k(f32x4& acc, FA fa, FB fb) {
 }
 
 template <int E> constexpr int bwd_waves() { return E >= 8 ? 8 : 4; }
+// The reverse recurrence with two slices a tile (PK, see k_bwd_rec).
+template <typename T, int KD, int C, int E>
+constexpr bool rec_pk() { return sizeof(T) == 2 && E == 16 && KD >= 64; }
 
 // ============================================================ reverse recurrence
 template <typename T, int KD, int C, int E, int NW>
@@ -125,7 +128,8 @@ struct RecSmem {
 // dO tile is transposed here.  Loads are unconditional (rows past T read a
 // clamped row and are zeroed when stored) and waves past the last piece of a
 // loop step skip it (a scalar branch).
-template <typename T, int KD, int C, int E, int NTHR>
+// PK: the dO tile is the workgroup's 8 columns, kept twice (columns c and c + 8).
+template <typename T, int KD, int C, int E, int NTHR, bool PK = false>
 struct RecStage {
   typedef OpTiles<T, KD, C> OT;
   static constexpr int EC = 16 / (int)sizeof(T);        // elements per 16-byte chunk
@@ -136,7 +140,8 @@ struct RecStage {
   static constexpr int NR = (NRC + NTHR - 1) / NTHR;
   static constexpr int NTT = (NTC + NTHR - 1) / NTHR;
   static constexpr int NM = (NMC + NTHR - 1) / NTHR;
-  static constexpr int NDB = (RB * 4 + NTHR - 1) / NTHR;       // 4 x 4 blocks of the dO tile
+  static constexpr int CB = PK ? 2 : 4;                         // 4-column blocks of the dO tile
+  static constexpr int NDB = (RB * CB + NTHR - 1) / NTHR;      // 4 x 4 blocks of the dO tile
   static constexpr int NCB = (3 * E * C / 4 + NTHR - 1) / NTHR;
   static constexpr int E4 = (E + 3) & ~3;
   static constexpr int DW = sizeof(T) == 2 ? 2 : 4;            // words per 4 elements
@@ -173,8 +178,8 @@ struct RecStage {
       }
 #pragma unroll
       for (int i = 0; i < NDB; ++i) {
-        if (w0 + i * NTHR >= RB * 4) continue;
-        const int blk = min(tid + i * NTHR, RB * 4 - 1);
+        if (w0 + i * NTHR >= RB * CB) continue;
+        const int blk = min(tid + i * NTHR, RB * CB - 1);
         const int rb = blk % RB, c4 = blk / RB;
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr) {
@@ -225,7 +230,7 @@ struct RecStage {
     for (int i = 0; i < NDB; ++i) {
       const int blk = tid + i * NTHR;
       const int rb = blk % RB, c4 = blk / RB;
-      if (blk < RB * 4) {
+      if (blk < RB * CB) {
         uint32_t dd[4][DW];
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr) {
@@ -234,9 +239,13 @@ struct RecStage {
           for (int j = 0; j < DW; ++j) dd[rr][j] = ok ? d[i][rr][j] : 0u;
         }
 #pragma unroll
-        for (int cc = 0; cc < 4; ++cc)
+        for (int cc = 0; cc < 4; ++cc) {
           lds_put4(&sm.dOt[4 * c4 + cc][4 * rb], word_elem<T>(dd[0], cc), word_elem<T>(dd[1], cc),
                    word_elem<T>(dd[2], cc), word_elem<T>(dd[3], cc));
+          if constexpr (PK)
+            lds_put4(&sm.dOt[8 + 4 * c4 + cc][4 * rb], word_elem<T>(dd[0], cc), word_elem<T>(dd[1], cc),
+                     word_elem<T>(dd[2], cc), word_elem<T>(dd[3], cc));
+        }
       }
     }
     }
@@ -271,18 +280,27 @@ struct RecStage {
 // bf16 tiles (dSck, dSck_lo).  A given final-state gradient makes dS' of the
 // last chunks far larger than elsewhere in the sequence, and one bf16
 // rounding of it would then dominate the gradients of those chunks.
-template <typename T, int KD, int C, int E, int NW, bool PDS>
+//
+// PK (bf16, E = 16): an accumulator tile holds two key slices side by side, 8
+// value columns each (columns 0..7 slice 2 u, 8..15 slice 2 u + 1 of "unit" u),
+// so that a wave owns one unit with the registers and the shared memory of the
+// E = 8 instance: its inputs come a chunk ahead again and nothing spills, and
+// twice the workgroups run.  One wave with two slices of 16 columns spilled and
+// loaded each chunk's inputs at its own start: B2 T2048 H16 E16 1256 -> 435 us.
+template <typename T, int KD, int C, int E, int NW, bool PDS, bool PK>
 __global__ __launch_bounds__(NW * 64) void k_bwd_rec(Shape s, FwdIn in, const void* dOv,
                                                      const float* dS_final, PrepBufs p,
                                                      BwdBufs bb, float* ds0) {
-  constexpr int SPW = (E + NW - 1) / NW;
-  constexpr bool RAGGED = E % NW != 0;  // some waves own fewer slices
+  constexpr int UE = PK ? E / 2 : E;    // slices or slice pairs
+  constexpr int SPW = (UE + NW - 1) / NW;
+  constexpr bool RAGGED = UE % NW != 0;  // some waves own fewer slices
   constexpr int NT = C / 16;
   constexpr int KT = KD / 16;
   constexpr int NTHR = NW * 64;
+  constexpr int VW = PK ? 8 : 16;       // value columns of a workgroup
   typedef typename Elem<T>::frag F;
   typedef RecSmem<T, KD, C, E, NW> Sm;
-  // eight-wave instances (E = 16) have half the registers per lane: they load
+  // eight-wave instances with several slices a wave have half the registers per lane: they load
   // each chunk's inputs at its own start instead of one chunk ahead, and
   // reuse operand fragments over fewer slices at a time
   constexpr bool PREFETCH = SPW == 1 || NW <= 4;
@@ -296,9 +314,11 @@ __global__ __launch_bounds__(NW * 64) void k_bwd_rec(Shape s, FwdIn in, const vo
   const int w = wave_id(), l = lane_id(), g = l >> 4, n = l & 15;
   const int V = s.V;
   int head, vt;
-  xcd_map(blockIdx.x, s.NH, V / 16, head, vt);
+  xcd_map(blockIdx.x, s.NH, V / VW, head, vt);
   const int b = head / s.H, h = head % s.H;
-  const int v0 = vt * 16;
+  const int v0 = vt * VW;
+  const int vc = PK ? (n & 7) : n;  // this lane's value column, and its slice of unit u
+  auto slc = [&](int u) { return PK ? 2 * u + (n >> 3) : u; };
   const size_t tok0 = seq_begin(s, b);
   s.T = seq_len(s, b);                 // this sequence's length from here on
   const int nc = (s.T + C - 1) / C;    // its chunks (s.Nc: the per-head stride)
@@ -307,12 +327,12 @@ __global__ __launch_bounds__(NW * 64) void k_bwd_rec(Shape s, FwdIn in, const vo
   f32x4 dS[SPW][KT];
 #pragma unroll
   for (int i = 0; i < SPW; ++i) {
-    const int e = w * SPW + i;
+    const int e = slc(w * SPW + i);
 #pragma unroll
     for (int kt = 0; kt < KT; ++kt) {
       f32x4 x = zero4();
       if (dS_final && e < E) {
-        const float* src = dS_final + (((size_t)head * E + e) * KD + key_col<KD>(kt, g)) * V + v0 + n;
+        const float* src = dS_final + (((size_t)head * E + e) * KD + key_col<KD>(kt, g)) * V + v0 + vc;
 #pragma unroll
         for (int j = 0; j < 4; ++j) x[j] = src[(size_t)j * V];
       }
@@ -330,12 +350,22 @@ __global__ __launch_bounds__(NW * 64) void k_bwd_rec(Shape s, FwdIn in, const vo
   auto store_dudw = [&](size_t chs) {
     if (w < NT) {
       const int rt = w;
-      store_tile16(bb.dU + chs * C * (size_t)V + (size_t)(16 * rt) * V + v0, sm.dUf[rt][l], g, n, V);
-      if (s.variant == 1)  // (sGLA: dW = 0, never read)
-        store_tile16(bb.dW + chs * C * (size_t)V + (size_t)(16 * rt) * V + v0, sm.dWs[rt][l], g, n, V);
+      const size_t off = chs * C * (size_t)V + (size_t)(16 * rt) * V + v0;
+      if constexpr (PK) {  // columns 8..15 repeat 0..7
+        const f32x4 u = quad_transpose(sm.dUf[rt][l], n), x = quad_transpose(sm.dWs[rt][l], n);
+        const size_t o = off + (size_t)(4 * g + (n & 3)) * V + 4 * (n >> 2);
+        if (n < 8) {
+          gstore_b128(bb.dU + o, __builtin_bit_cast(u32x4, u));
+          if (s.variant == 1) gstore_b128(bb.dW + o, __builtin_bit_cast(u32x4, x));
+        }
+      } else {
+        store_tile16(bb.dU + off, sm.dUf[rt][l], g, n, V);
+        if (s.variant == 1)  // (sGLA: dW = 0, never read)
+          store_tile16(bb.dW + off, sm.dWs[rt][l], g, n, V);
+      }
     }
   };
-  RecStage<T, KD, C, E, NTHR> stage;
+  RecStage<T, KD, C, E, NTHR, PK> stage;
   if constexpr (PREFETCH)
     if (nc > 0) stage.load(s, p, Kg, Qg, dOg, (size_t)head * s.Nc + nc - 1, nc - 1);
   for (int ci = nc - 1; ci >= 0; --ci) {
@@ -348,7 +378,7 @@ __global__ __launch_bounds__(NW * 64) void k_bwd_rec(Shape s, FwdIn in, const vo
     } else {
 #pragma unroll
       for (int part = 1; part <= 2; ++part) {  // in halves: fewer live registers
-        RecStage<T, KD, C, E, NTHR> now;
+        RecStage<T, KD, C, E, NTHR, PK> now;
         now.load(s, p, Kg, Qg, dOg, ch, ci, part);
         now.store(sm, s.variant, t0, s.T, part);
       }
@@ -372,12 +402,25 @@ __global__ __launch_bounds__(NW * 64) void k_bwd_rec(Shape s, FwdIn in, const vo
 #pragma unroll
     for (int i = 0; i < SPW; ++i) {
       const int e = w * SPW + i;
-      if (RAGGED && e >= E) continue;
+      if (RAGGED && e >= UE) continue;
       const size_t toff = ((ch * E + e) * (size_t)(V / 16) + vt) * KD * 16;
       T* dst = (T*)bb.dSck + toff;
 #pragma unroll
       for (int kt = 0; kt < KT; ++kt) {
-        if constexpr (sizeof(T) == 2) {
+        if constexpr (PK) {
+          // the transposed tile: lane (g, n) holds row n, columns 4 g .. + 3, of
+          // slice 2 u + g / 2; a 16 x 16 block keeps its column halves one after the other
+          const size_t o = ((ch * E + 2 * e + (g >> 1)) * (size_t)(V / 16) + (vt >> 1)) * KD * 16 + 256 * kt +
+                           128 * (vt & 1) + 8 * n + 4 * (g & 1);
+          f32x4 t = zero4();
+          mma16(t, dSop[i][kt], idf);
+          gstore_b64((T*)bb.dSck + o, __builtin_bit_cast(u32x2, cvt_frag<bf16_t>(t)));
+          if constexpr (PDS) {
+            f32x4 tl = zero4();
+            mma16(tl, dSlo[i][kt], idf);
+            gstore_b64((T*)bb.dSck_lo + o, __builtin_bit_cast(u32x2, cvt_frag<bf16_t>(tl)));
+          }
+        } else if constexpr (sizeof(T) == 2) {
           store_tile16_frag(dst + 256 * kt, dSop[i][kt], idf, g, n);
           if constexpr (PDS) store_tile16_frag((T*)bb.dSck_lo + toff + 256 * kt, dSlo[i][kt], idf, g, n);
         } else {
@@ -426,7 +469,7 @@ __global__ __launch_bounds__(NW * 64) void k_bwd_rec(Shape s, FwdIn in, const vo
           const Frag8<T> kk = kfrag8(kb);
 #pragma unroll
           for (int i = i0; i < i0 + GZ; ++i)
-            if (!RAGGED || w * SPW + i < E) {
+            if (!RAGGED || w * SPW + i < UE) {
               mma32(z[i], kk, dSop[i][kb], dSop[i][kb + 1]);
               if constexpr (PDS) mma32(z[i], kk, dSlo[i][kb], dSlo[i][kb + 1]);
             }
@@ -435,7 +478,7 @@ __global__ __launch_bounds__(NW * 64) void k_bwd_rec(Shape s, FwdIn in, const vo
           const F k0 = kfrag(KT - 1);
 #pragma unroll
           for (int i = i0; i < i0 + GZ; ++i)
-            if (!RAGGED || w * SPW + i < E) {
+            if (!RAGGED || w * SPW + i < UE) {
               mma16(z[i], k0, dSop[i][KT - 1]);
               if constexpr (PDS) mma16(z[i], k0, dSlo[i][KT - 1]);
             }
@@ -444,8 +487,12 @@ __global__ __launch_bounds__(NW * 64) void k_bwd_rec(Shape s, FwdIn in, const vo
       f32x4 acc = zero4();
 #pragma unroll
       for (int i = 0; i < SPW; ++i) {
-        const int e = w * SPW + i;
-        if (!RAGGED || e < E) acc += *(const f32x4*)&sm.coef[2][e][16 * rt + 4 * g] * z[i];
+        const int u = w * SPW + i;
+        if (!RAGGED || u < UE) acc += *(const f32x4*)&sm.coef[2][slc(u)][16 * rt + 4 * g] * z[i];
+      }
+      if constexpr (PK) {  // both slices of the unit
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[j] += dpp_f<0x128>(acc[j]);  // row_ror:8
       }
       sm.X[w][rt][l] = acc;
     }
@@ -536,8 +583,8 @@ __global__ __launch_bounds__(NW * 64) void k_bwd_rec(Shape s, FwdIn in, const vo
         float gcs[GS];
 #pragma unroll
         for (int ii = 0; ii < GS; ++ii) {
-          const int e = w * SPW + i0 + ii;
-          if (RAGGED && e >= E) continue;
+          if (RAGGED && w * SPW + i0 + ii >= UE) continue;
+          const int e = slc(w * SPW + i0 + ii);
           gcs[ii] = sm.gC[e];
 #pragma unroll
           for (int kb = 0; kb < NT; ++kb) {
@@ -575,7 +622,7 @@ __global__ __launch_bounds__(NW * 64) void k_bwd_rec(Shape s, FwdIn in, const vo
           for (int kb = 0; kb + 1 < NT; kb += 2) {
 #pragma unroll
             for (int ii = 0; ii < GS; ++ii) {
-              if (RAGGED && w * SPW + i0 + ii >= E) continue;
+              if (RAGGED && w * SPW + i0 + ii >= UE) continue;
               mma32(acc[ii], q[kb], q[kb + 1], bh[ii][kb], bh[ii][kb + 1]);
               if constexpr (Sm::SPLIT) mma32(acc[ii], q[kb], q[kb + 1], bl[ii][kb], bl[ii][kb + 1]);
               if constexpr (GDN) {
@@ -588,7 +635,7 @@ __global__ __launch_bounds__(NW * 64) void k_bwd_rec(Shape s, FwdIn in, const vo
             const int kb = NT - 1;
 #pragma unroll
             for (int ii = 0; ii < GS; ++ii) {
-              if (RAGGED && w * SPW + i0 + ii >= E) continue;
+              if (RAGGED && w * SPW + i0 + ii >= UE) continue;
               mma16(acc[ii], q[kb], bh[ii][kb]);
               if constexpr (Sm::SPLIT) mma16(acc[ii], q[kb], bl[ii][kb]);
               if constexpr (GDN) {
@@ -599,7 +646,7 @@ __global__ __launch_bounds__(NW * 64) void k_bwd_rec(Shape s, FwdIn in, const vo
           }
 #pragma unroll
           for (int ii = 0; ii < GS; ++ii)
-            if (!RAGGED || w * SPW + i0 + ii < E) dS[i0 + ii][kt] = acc[ii];
+            if (!RAGGED || w * SPW + i0 + ii < UE) dS[i0 + ii][kt] = acc[ii];
         }
       }
     };
@@ -613,11 +660,11 @@ __global__ __launch_bounds__(NW * 64) void k_bwd_rec(Shape s, FwdIn in, const vo
   if (ds0) {
 #pragma unroll
     for (int i = 0; i < SPW; ++i) {
-      const int e = w * SPW + i;
-      if (RAGGED && e >= E) continue;
+      if (RAGGED && w * SPW + i >= UE) continue;
+      const int e = slc(w * SPW + i);
 #pragma unroll
       for (int kt = 0; kt < KT; ++kt) {
-        float* dst = ds0 + (((size_t)head * E + e) * KD + key_col<KD>(kt, g)) * V + v0 + n;
+        float* dst = ds0 + (((size_t)head * E + e) * KD + key_col<KD>(kt, g)) * V + v0 + vc;
 #pragma unroll
         for (int j = 0; j < 4; ++j) dst[(size_t)j * V] = dS[i][kt][j];
       }
@@ -809,13 +856,17 @@ __global__ __launch_bounds__(STATE_NTHR) void k_bwd_state(Shape s, FwdIn in, con
   const T* dSck = (const T*)bb.dSck;
   const T* dSlk = (const T*)bb.dSck_lo;
   Raw8<T> sbuf[CTW][NPMAX], dbuf[CTW][NPMAX], dlbuf[PDS ? CTW : 1][PDS ? NPMAX : 1];
+  // dS' of the 8-column recurrence keeps the two column halves of a 16 x 16
+  // block one after the other
+  constexpr bool HALF = rec_pk<T, KD, C, E>();
+  const int lnD = 8 * n + 128 * (g & 1) - (16 * n + 8 * (g & 1));  // this lane's piece against Sck's order
   auto load_pair = [&](int e, int c, int pp) {
     const int ct = min(q * CTW + c, KT - 1);
     const int vb = min(2 * pp + (g >> 1), VB - 1);
     const size_t off = ((((size_t)ch * E + e) * VB + vb) * KD + 16 * ct + n) * 16 + 8 * (g & 1);
     sbuf[c][pp] = load8(Sck + off);
-    dbuf[c][pp] = load8(dSck + off);
-    if constexpr (PDS) dlbuf[c][pp] = load8(dSlk + off);
+    dbuf[c][pp] = load8(dSck + off + (HALF ? lnD : 0));
+    if constexpr (PDS) dlbuf[c][pp] = load8(dSlk + off + (HALF ? lnD : 0));
   };
 #pragma unroll
   for (int pp = 0; pp < NPMAX; ++pp)
@@ -1831,16 +1882,17 @@ template <typename T, int KD, int C, int E>
 static hipError_t rec_inst(const Shape& s, const FwdIn& in, const void* dO, const float* dSf,
                            const PrepBufs& p, const BwdBufs& bb, float* ds0, hipStream_t st) {
   constexpr int NW = bwd_waves<E>();
+  constexpr bool PK = rec_pk<T, KD, C, E>();
   const size_t smem = sizeof(RecSmem<T, KD, C, E, NW>);
   auto go = [&](auto pds_c) {
     constexpr bool PDS = decltype(pds_c)::value;
     static bool attr = false;
     if (!attr) {
-      (void)hipFuncSetAttribute((const void*)k_bwd_rec<T, KD, C, E, NW, PDS>,
+      (void)hipFuncSetAttribute((const void*)k_bwd_rec<T, KD, C, E, NW, PDS, PK>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
       attr = true;
     }
-    hipLaunchKernelGGL((k_bwd_rec<T, KD, C, E, NW, PDS>), dim3(s.NH * (s.V / 16)), dim3(NW * 64),
+    hipLaunchKernelGGL((k_bwd_rec<T, KD, C, E, NW, PDS, PK>), dim3(s.NH * (s.V / (PK ? 8 : 16))), dim3(NW * 64),
                        smem, st, s, in, dO, dSf, p, bb, ds0);
     return hipGetLastError();
   };
