@@ -163,7 +163,7 @@ tla::PrepBufs prep_bufs(const Layout& L, const void* base, bool ninv) {
   char* b = (char*)base;
   return tla::PrepBufs{(float*)(b + L.p_coef), (float*)(b + L.p_gC), (void*)(b + L.p_ops),
                        (ninv && L.p_ninv < L.p_size) ? (float*)(b + L.p_ninv) : nullptr,
-                       ninv ? 1 : 0, nullptr};
+                       ninv ? 1 : 0};
 }
 tla::SavedBufs saved_bufs(const Layout& L, const void* saved) {
   char* b = (char*)saved;
@@ -340,7 +340,7 @@ static int fwd_impl(const tla_desc* d, const int32_t* cu, long long total, const
   if (ntok > 0 || s_final) {
     tla::SavedBufs sv = saved_bufs(L, saved);
     e = timed(PROF_FWD, st, [&] {
-      return la ? tla::launch_fwd_la(s, in, pb, o, s_final, nullptr, st)
+      return la ? tla::launch_fwd_la(s, in, pb, o, s_final, st)
                 : tla::launch_fwd(s, in, pb, o, s_final, saved ? &sv : nullptr, st);
     });
     if (e != hipSuccess) return device_fail(e, "forward kernel");

@@ -48,7 +48,6 @@ struct PrepBufs {
   void* ops;     // [ch][op_tile_elems] operand tiles, see OpTiles
   float* ninv;   // [ch][C][C]     (I + L)^{-1} in fp32 (GDN training forward), or NULL
   int bwd_tiles; // training forward: also write Q^T (read only by the backward)
-  void* bops;    // look-ahead instances, training forward: the backward's tiles (LaOps), else NULL
 };
 
 // Operand tiles of one chunk, in the operand type T and in the layouts the
@@ -107,11 +106,11 @@ inline int round4(int x) { return (x + 3) & ~3; }
 hipError_t launch_prep(const Shape& s, const FwdIn& in, const PrepBufs& p, hipStream_t st);
 hipError_t launch_fwd(const Shape& s, const FwdIn& in, const PrepBufs& p, void* o,
                       float* s_final, const SavedBufs* saved, hipStream_t st);
-// The look-ahead instances (bf16 operands, K >= 64): prep and forward.
+// The look-ahead instances (inference, bf16 operands, K >= 64): prep and forward.
 bool la_instance(int K, int C, int E, bool bf16);
 hipError_t launch_prep_la(const Shape& s, const FwdIn& in, const PrepBufs& p, hipStream_t st);
 hipError_t launch_fwd_la(const Shape& s, const FwdIn& in, const PrepBufs& p, void* o,
-                         float* s_final, const SavedBufs* saved, hipStream_t st);
+                         float* s_final, hipStream_t st);
 hipError_t launch_bwd_rec(const Shape& s, const FwdIn& in, const void* dO, const float* dS_final,
                           const PrepBufs& p, const BwdBufs& bb, float* ds0, hipStream_t st);
 hipError_t launch_bwd_state(const Shape& s, const FwdIn& in, const void* dO, const PrepBufs& p,

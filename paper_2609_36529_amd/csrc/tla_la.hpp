@@ -8,23 +8,20 @@
 //   G_{c+1} = (K_{c+1} K_c^T) o sum_e a_{c+1,e} c_{c,e}^T        (C x C),
 // the state contraction uses the state one chunk back, so it runs beside the
 // update instead of after it, and only the two C x C products G U and Tu X
-// remain on the chain.  The reverse recurrence has the same form with G^T
-// and, for the queries, H_{c+1} = (Q_{c+1} K_c^T) o sum_e b_{c+1,e} c_{c,e}^T.
+// remain on the chain.
 #pragma once
 #include "tla_common.hpp"
 #include "tla_internal.hpp"
 
 namespace tla {
 
-// Operand tiles of one chunk.  M and Tu (lower block-triangular), G and H are
+// Operand tiles of one chunk.  M and Tu (lower block-triangular) and G are
 // kept as bf16 (hi, lo) pairs of 32-deep A operands, 1 KiB each: lane (g, n) of
 // operand (rt, p) holds row 16 rt + n at columns 32 p + 4 g + j (elements
 // 0..3) and 32 p + 16 + 4 g + j (elements 4..7), the order in which two
-// accumulator tiles make a 32-deep B operand.  H is kept transposed (rows:
-// positions of chunk c - 1, columns: positions of chunk c).  K^T and Q^T are
+// accumulator tiles make a 32-deep B operand.  K^T is
 // [K][C] with row R holding key la_key(R) and the 16-byte pieces of a row in
-// the order of SwzTile, so that a plain copy fills the shared tile.  H and Q^T
-// serve the backward and live in a region of their own.
+// the order of SwzTile, so that a plain copy fills the shared tile.
 template <int KD, int C>
 struct LaOps {
   static constexpr int NT = C / 16, NP = NT / 2;
@@ -37,8 +34,6 @@ struct LaOps {
   static constexpr size_t M = 0, Tu = (size_t)NTRI * 2 * FR, G = 2 * Tu;
   static constexpr size_t Kt = G + (size_t)NT * NP * 2 * FR;
   static constexpr size_t STRIDE = Kt + (size_t)KD * C;
-  static constexpr size_t H = 0, Qt = (size_t)NT * NP * 2 * FR;  // backward region
-  static constexpr size_t BSTRIDE = Qt + (size_t)KD * C;
 };
 
 // Key order of the state tiles.  Row m of a 32-row accumulator tile lies in

@@ -13,7 +13,7 @@ namespace tla {
 // with every C x C tile formed transposed on the matrix cores (A: the rows of
 // the columns' side), so that an accumulator is already the A operand that
 // the recurrences read and leaves as whole 16-byte pieces without a shared
-// copy, and with the tiles G (and H) between this chunk and the one before.
+// copy, and with the tiles G between this chunk and the one before.
 template <int KD, int C, int E>
 struct LaPrepSmem {
   static constexpr int KP = KD + 8;  // 16-byte rows, conflict-free 16-byte fragment reads
@@ -70,9 +70,8 @@ __global__ __launch_bounds__(la_prep_waves<E>() * 64, E <= 8 ? 4 : 2) void k_pre
   const T* Kg = (const T*)in.k + (tok0 * s.H + h) * KD;
   const size_t eoff = (tok0 * s.H + h) * E, erow = (size_t)s.H * E;
   const bool prev = ci > 0;  // the chunk before is a whole one
-  // G couples the retrieval of this chunk to the chunk before (GDN), H the
-  // queries (backward only)
-  const bool need_g = prev && s.variant == 1, need_h = prev && p.bops != nullptr;
+  // G couples the retrieval of this chunk to the chunk before (GDN)
+  const bool need_g = prev && s.variant == 1;
 
   // ---- every global load of the phase before the first of the stores
   constexpr int NQE = (C * E + NTHR - 1) / NTHR;
@@ -100,7 +99,7 @@ __global__ __launch_bounds__(la_prep_waves<E>() * 64, E <= 8 ? 4 : 2) void k_pre
     qv[it] = load8(Qg + off);
     kv[it] = load8(Kg + off);
   }
-  const int tp = need_g || need_h ? t0 - C : t0;  // first position of the chunk before (or, not needed, of this one)
+  const int tp = need_g ? t0 - C : t0;  // first position of the chunk before (or, not needed, of this one)
 #pragma unroll
   for (int i = 0; i < NGE; ++i) {
     const int e = min(w + NW * i, E - 1);
@@ -257,77 +256,45 @@ __global__ __launch_bounds__(la_prep_waves<E>() * 64, E <= 8 ? 4 : 2) void k_pre
     }
     store_op(ops + OT::M + (size_t)pair * 2 * OT::FR + 8 * l, mv[0], mv[1]);
   }
-  // ---- G and H: K rows of the chunk before from global memory, the rank-E
+  // ---- G: K rows of the chunk before from global memory, the rank-E
   // factor sum_e a_e c_e^T on the fp32 MFMA (four slices a step)
-  if (need_g || need_h) {
+  if (need_g) {
     for (int pair = w; pair < NT * NP; pair += NW) {
       const int rt = pair / NP, pp = pair % NP;
       static_assert(NW % NP == 0, "every pair of a wave has the same columns");
-      // a_e (or b_e) of row r and c_e of row r of the chunk before, slice 4 q + g
-      auto av = [&](const float(*x2)[E], int r, int q) {
-        return x2[r][4 * q + g] * exp_nonpos((float)sm.G[r][4 * q + g]);
+      // a_e of row r, slice 4 q + g
+      auto av = [&](int r, int q) {
+        return sm.k2[r][4 * q + g] * exp_nonpos((float)sm.G[r][4 * q + g]);
       };
-      if (need_g) {  // rows r of this chunk (tile rt), columns s of the one before (tiles 2 pp, 2 pp + 1)
-        f32x4 x[2];
+      // rows r of this chunk (tile rt), columns s of the one before (tiles 2 pp, 2 pp + 1)
+      f32x4 x[2];
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-          f32x4 ak = zero4(), rr = zero4();
+      for (int hh = 0; hh < 2; ++hh) {
+        f32x4 ak = zero4(), rr = zero4();
 #pragma unroll
-          for (int kb = 0; kb < KB; ++kb) mma8(ak, kp[hh][kb], krow8(16 * rt + n, 32 * kb + 8 * g));
+        for (int kb = 0; kb < KB; ++kb) mma8(ak, kp[hh][kb], krow8(16 * rt + n, 32 * kb + 8 * g));
 #pragma unroll
-          for (int q = 0; q < E / 4; ++q)
-            rr = __builtin_amdgcn_mfma_f32_16x16x4f32(sm.cp[16 * (2 * pp + hh) + n][4 * q + g],
-                                                      av(sm.k2, 16 * rt + n, q), rr, 0, 0, 0);
-          x[hh] = ak * rr;
-        }
-        store_op(ops + OT::G + (size_t)OT::full(rt, pp) * 2 * OT::FR + 8 * l, x[0], x[1]);
+        for (int q = 0; q < E / 4; ++q)
+          rr = __builtin_amdgcn_mfma_f32_16x16x4f32(sm.cp[16 * (2 * pp + hh) + n][4 * q + g],
+                                                    av(16 * rt + n, q), rr, 0, 0, 0);
+        x[hh] = ak * rr;
       }
-      if (need_h) {  // rows s of the chunk before (tile st), columns r of this one (tiles 2 pr, 2 pr + 1)
-        const int st = 2 * pp + (rt & 1), pr = rt >> 1;
-        Raw8<T> ks[KB];
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb) {
-          const bool odd = rt & 1;
-          ks[kb].w[0].x = odd ? kp[1][kb].w[0].x : kp[0][kb].w[0].x;
-          ks[kb].w[0].y = odd ? kp[1][kb].w[0].y : kp[0][kb].w[0].y;
-          ks[kb].w[0].z = odd ? kp[1][kb].w[0].z : kp[0][kb].w[0].z;
-          ks[kb].w[0].w = odd ? kp[1][kb].w[0].w : kp[0][kb].w[0].w;
-        }
-        f32x4 x[2];
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-          const int r = 16 * (2 * pr + hh) + n;
-          f32x4 aq = zero4(), rr = zero4();
-#pragma unroll
-          for (int kb = 0; kb < KB; ++kb) mma8(aq, qrow8(r, 32 * kb + 8 * g), ks[kb]);
-#pragma unroll
-          for (int q = 0; q < E / 4; ++q)
-            rr = __builtin_amdgcn_mfma_f32_16x16x4f32(av(sm.q2, r, q), sm.cp[16 * st + n][4 * q + g], rr,
-                                                      0, 0, 0);
-          x[hh] = aq * rr;
-        }
-        store_op((T*)p.bops + (size_t)ch * OT::BSTRIDE + OT::H + (size_t)OT::full(st, pr) * 2 * OT::FR + 8 * l,
-                 x[0], x[1]);
-      }
+      store_op(ops + OT::G + (size_t)OT::full(rt, pp) * 2 * OT::FR + 8 * l, x[0], x[1]);
     }
   }
-  // ---- K^T (and for the backward Q^T), read out of the staged rows column-wise
-  const int nmat = p.bops ? 2 : 1;
-  for (int idx = tid; idx < nmat * KD * C / 8; idx += NTHR) {
-    const int mtx = idx / (KD * C / 8), rem = idx % (KD * C / 8);
+  // ---- K^T, read out of the staged rows column-wise
+  for (int idx = tid; idx < KD * C / 8; idx += NTHR) {
     int R, c8;
-    SwzTile<T, KD, C>::logical(rem, R, c8);
+    SwzTile<T, KD, C>::logical(idx, R, c8);
     const int key = la_key(R);
     uint32_t wd[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int p0 = 8 * c8 + 2 * i;
-      const uint16_t v0 = mtx ? sm.u.qk.sQ[p0][key] : sm.u.qk.sK[p0][key];
-      const uint16_t v1 = mtx ? sm.u.qk.sQ[p0 + 1][key] : sm.u.qk.sK[p0 + 1][key];
+      const uint16_t v0 = sm.u.qk.sK[p0][key], v1 = sm.u.qk.sK[p0 + 1][key];
       wd[i] = (uint32_t)v0 | ((uint32_t)v1 << 16);
     }
-    T* dst = mtx ? (T*)p.bops + (size_t)ch * OT::BSTRIDE + OT::Qt : ops + OT::Kt;
-    gstore_b128(dst + (size_t)8 * rem, u32x4{wd[0], wd[1], wd[2], wd[3]});
+    gstore_b128(ops + OT::Kt + (size_t)8 * idx, u32x4{wd[0], wd[1], wd[2], wd[3]});
   }
   if (s.variant != 1) return;
   __syncthreads();
@@ -335,13 +302,6 @@ __global__ __launch_bounds__(la_prep_waves<E>() * 64, E <= 8 ? 4 : 2) void k_pre
   // ---- Tu = (I + L)^{-1} diag(beta), blocked unit-lower inverse in fp32
   unit_lower_inverse<C, NTHR>([&](int r, int c) { return sm.L[r][c]; }, &sm.u.inv.X[0][0], Sm::CP,
                               &sm.u.inv.Y[0][0][0]);
-  if (p.ninv) {  // kept in fp32 for the backward of the solve
-    float* dst = p.ninv + (size_t)ch * C * C;
-    for (int idx = tid; idx < C * C / 4; idx += NTHR) {
-      const int r = idx / (C / 4), c4 = idx % (C / 4);
-      gstore_b128(dst + r * C + 4 * c4, __builtin_bit_cast(u32x4, *(const f32x4*)&sm.u.inv.X[r][4 * c4]));
-    }
-  }
   for (int pair = w; pair < OT::NTRI; pair += NW) {
     int rt = 0;
     while (OT::tri(rt + 1, 0) <= pair) ++rt;
@@ -407,9 +367,9 @@ struct LaFwdSmem {
   alignas(16) bf16_t Xo[2][C][16];   // X_{c+1} likewise
 };
 
-template <int KD, int C, int E, bool PK, bool GDN, bool TRAIN>
+template <int KD, int C, int E, bool PK, bool GDN>
 __global__ __launch_bounds__(512, 2) void k_fwd_la(Shape s, FwdIn in, PrepBufs p, void* out,
-                                                   float* s_final, SavedBufs sv) {
+                                                   float* s_final) {
   typedef bf16_t T;
   typedef LaFwdSmem<KD, C, E, PK> Sm;
   typedef LaOps<KD, C> OT;
@@ -762,6 +722,7 @@ static void lds_limit(size_t smem) {
 
 template <int KD, int C, int E>
 static hipError_t prep_la(const Shape& s, const FwdIn& in, const PrepBufs& p, hipStream_t st) {
+  static_assert(LaOps<KD, C>::STRIDE <= OpTiles<bf16_t, KD, C>::STRIDE, "the tiles fit the workspace");
   const size_t smem = sizeof(LaPrepSmem<KD, C, E>);
   lds_limit<k_prep_la<KD, C, E>>(smem);
   hipLaunchKernelGGL((k_prep_la<KD, C, E>), dim3(s.NH * s.Nc), dim3(la_prep_waves<E>() * 64), smem, st, s,
@@ -769,25 +730,24 @@ static hipError_t prep_la(const Shape& s, const FwdIn& in, const PrepBufs& p, hi
   return hipGetLastError();
 }
 
-template <int KD, int C, int E, bool PK, bool GDN, bool TRAIN>
+template <int KD, int C, int E, bool PK, bool GDN>
 static hipError_t fwd_la2(const Shape& s, const FwdIn& in, const PrepBufs& p, void* o, float* s_final,
-                          const SavedBufs& sv, hipStream_t st) {
+                          hipStream_t st) {
   const size_t smem = sizeof(LaFwdSmem<KD, C, E, PK>);
   static_assert(sizeof(LaFwdSmem<KD, C, E, PK>) <= 160 * 1024, "shared-memory plan");
-  lds_limit<k_fwd_la<KD, C, E, PK, GDN, TRAIN>>(smem);
-  hipLaunchKernelGGL((k_fwd_la<KD, C, E, PK, GDN, TRAIN>), dim3(s.NH * (s.V / (PK ? 8 : 16))), dim3(512),
-                     smem, st, s, in, p, o, s_final, sv);
+  lds_limit<k_fwd_la<KD, C, E, PK, GDN>>(smem);
+  hipLaunchKernelGGL((k_fwd_la<KD, C, E, PK, GDN>), dim3(s.NH * (s.V / (PK ? 8 : 16))), dim3(512),
+                     smem, st, s, in, p, o, s_final);
   return hipGetLastError();
 }
 
 template <int KD, int C, int E>
 static hipError_t fwd_la(const Shape& s, const FwdIn& in, const PrepBufs& p, void* o, float* s_final,
-                         const SavedBufs* sv, hipStream_t st) {
-  const SavedBufs none{nullptr, nullptr, nullptr};
+                         hipStream_t st) {
   auto go = [&](auto pk) {
     constexpr bool PK = decltype(pk)::value;
-    return s.variant == 1 ? fwd_la2<KD, C, E, PK, true, false>(s, in, p, o, s_final, none, st)
-                          : fwd_la2<KD, C, E, PK, false, false>(s, in, p, o, s_final, none, st);
+    return s.variant == 1 ? fwd_la2<KD, C, E, PK, true>(s, in, p, o, s_final, st)
+                          : fwd_la2<KD, C, E, PK, false>(s, in, p, o, s_final, st);
   };
   if constexpr (E >= 16) {  // four slices a unit: the state of a wave fits its registers only so
     return go(std::true_type{});
@@ -822,8 +782,8 @@ hipError_t launch_prep_la(const Shape& s, const FwdIn& in, const PrepBufs& p, hi
 }
 
 hipError_t launch_fwd_la(const Shape& s, const FwdIn& in, const PrepBufs& p, void* o, float* s_final,
-                         const SavedBufs* saved, hipStream_t st) {
-#define CALL_F(KD_, C_, E_) fwd_la<KD_, C_, E_>(s, in, p, o, s_final, saved, st)
+                         hipStream_t st) {
+#define CALL_F(KD_, C_, E_) fwd_la<KD_, C_, E_>(s, in, p, o, s_final, st)
   TLA_LA_FOR_EACH(CALL_F)
 #undef CALL_F
   return hipErrorInvalidValue;
