@@ -751,12 +751,12 @@ static hipError_t fwd_la(const Shape& s, const FwdIn& in, const PrepBufs& p, voi
   };
   if constexpr (E >= 16) {  // four slices a unit: the state of a wave fits its registers only so
     return go(std::true_type{});
-  } else if constexpr (E == 8) {
-    // 8-column workgroups while 16-column ones would leave half of the 256 CUs
-    // idle: 36 against 41 us for GDN at B1 H16 T777 (128 or 256 workgroups)
-    if (s.NH * (s.V / 16) <= 128) return go(std::true_type{});
-    return go(std::false_type{});
   } else {
+    // 8-column workgroups while 16-column ones would leave half of the 256 CUs
+    // idle: 36 against 41 us for GDN at B1 H16 T777 E8 (256 or 128 workgroups);
+    // whole forwards at E = 4: sGLA B1 H4 T65536 1.45 against 1.59 ms, GDN
+    // there 2.28 against 2.32 ms, sGLA B2 H8 T2048 60 against 63 us
+    if (s.NH * (s.V / 16) <= 128) return go(std::true_type{});
     return go(std::false_type{});
   }
 }

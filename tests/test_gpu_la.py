@@ -46,11 +46,12 @@ def test_lengths(variant, K, C, E, V, T):
     assert eo <= TOL and es <= TOL
 
 
+@pytest.mark.parametrize("E", [8, 4])
 @pytest.mark.parametrize("variant", [0, 1])
-def test_widths_agree(variant):
+def test_widths_agree(variant, E):
     """The 8-column workgroups (few heads) and the 16-column ones run the same
     chunk recurrence: the same head alone and among 24 others."""
-    inp = _inputs(variant, 3, 150, 8, 128, 128, 8, 64)
+    inp = _inputs(variant, 3, 150, 8, 128, 128, E, 64)
     o, sf = _fwd(variant, inp, 64)
     one = {k: (None if v is None else v[1:2].contiguous()) for k, v in inp.items()}
     o1, sf1 = _fwd(variant, one, 64)
