@@ -607,15 +607,32 @@ __global__ __launch_bounds__(512, 2) void k_fwd_la(Shape s, FwdIn in, PrepBufs p
       }
       return u;
     };
-    auto unit_sum = [&](f32x4 x) {  // PK: the two slices of a half unit (lane halves)
+    // Sums over slices run over the even and over the odd slices and add the
+    // two: with PK they lie in the two lane halves of a half unit, else in NS = 2
+    // sums.  One order for both widths, so that the width, which goes by the
+    // heads of the whole call, does not reach the results: a sequence gives the
+    // same bits alone and among others.
+    constexpr int NS = PK ? 1 : 2;
+    struct Sum { f32x4 p[NS]; };
+    auto zero_sum = [] {
+      Sum x;
+#pragma unroll
+      for (int i = 0; i < NS; ++i) x.p[i] = zero4();
+      return x;
+    };
+    auto total = [](const Sum& x) {
       if constexpr (PK) {
+        f32x4 r;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const auto y = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[j]), __float_as_uint(x[j]), false, false);
-          x[j] = __uint_as_float(y[0]) + __uint_as_float(y[1]);
+          const uint32_t b = __float_as_uint(x.p[0][j]);
+          const auto y = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+          r[j] = __uint_as_float(y[0]) + __uint_as_float(y[1]);
         }
+        return r;
+      } else {
+        return x.p[0] + x.p[1];
       }
-      return x;
     };
 
     if (rows) {
@@ -627,15 +644,15 @@ __global__ __launch_bounds__(512, 2) void k_fwd_la(Shape s, FwdIn in, PrepBufs p
       __syncthreads();  // B0: the copy of S_c (and, unless direct, U_c) is there
       if (direct(c)) {
         if (GDN && rows) {  // X_c = V_c - sum_e diag(a_e) K_c S_c
-          f32x4 ws = zero4();
+          Sum ws = zero_sum();
 #pragma unroll
           for (int u = 0; u < 2 * UE; ++u) {
             f32x4 P = zero4();
 #pragma unroll
             for (int k = 0; k < NX; ++k) P = mma_16(s_op(u, k), kf[k], P);
-            ws += sm.ca[c & 1][cslc(u)][row] * P;
+            ws.p[u % NS] += sm.ca[c & 1][cslc(u)][row] * P;
           }
-          put_x(c, v_row(c) - unit_sum(ws));
+          put_x(c, v_row(c) - total(ws));
           load_x(c + 1, c);
           load_full(go, OT::G, c + 1);
         }
@@ -680,16 +697,16 @@ __global__ __launch_bounds__(512, 2) void k_fwd_la(Shape s, FwdIn in, PrepBufs p
           qf[k] = *(const bf16x8*)(qr + 32 * k);
           if constexpr (GDN) kf[k] = *(const bf16x8*)(kr + 32 * k);
         }
-        f32x4 os = zero4(), ws = zero4();
+        Sum os = zero_sum(), ws = zero_sum();
 #pragma unroll
         for (int u = 0; u < 2 * UE; ++u) {
           const int e = cslc(u);
-          os += sm.cbc[c & 1][0][e][row] * PQ[u];
-          if constexpr (GDN) ws += (sm.gC[c & 1][e] * sm.ca[(c + 1) & 1][e][row]) * PK_[u];
+          os.p[u % NS] += sm.cbc[c & 1][0][e][row] * PQ[u];
+          if constexpr (GDN) ws.p[u % NS] += (sm.gC[c & 1][e] * sm.ca[(c + 1) & 1][e][row]) * PK_[u];
         }
         if constexpr (GDN)
-          if (ahead) put_x(c + 1, v_row(c + 1) - (unit_sum(ws) + x));
-        o += unit_sum(os);
+          if (ahead) put_x(c + 1, v_row(c + 1) - (total(ws) + x));
+        o += total(os);
       }
       __syncthreads();  // B1: X_{c+1}; every row wave is done with U_c and the copy of S_c
       if (rows) {
