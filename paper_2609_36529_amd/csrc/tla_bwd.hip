@@ -371,7 +371,7 @@ __global__ __launch_bounds__(NW * 64) void k_bwd_rec(Shape s, FwdIn in, const vo
   for (int ci = nc - 1; ci >= 0; --ci) {
     const int t0 = ci * C;
     const size_t ch = (size_t)head * s.Nc + ci;
-    __syncthreads();
+    block_sync();
     // ---- this chunk's inputs to LDS; the next chunk's loads go in flight
     if constexpr (PREFETCH) {
       stage.store(sm, s.variant, t0, s.T);
@@ -900,7 +900,7 @@ __global__ __launch_bounds__(STATE_NTHR) void k_bwd_state(Shape s, FwdIn in, con
       if (pp >= NP) continue;
       int col = 32 * pp;
       if constexpr (!Sm::STAGE_ALL) {
-        __syncthreads();
+        block_sync();
         stage(32 * pp, 32);
         __syncthreads();
         col = 0;

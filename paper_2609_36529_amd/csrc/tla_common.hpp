@@ -590,6 +590,18 @@ __device__ __forceinline__ void wait_vmcnt_rt(int n) {
 }
 __device__ __forceinline__ void wait_vmcnt_rt(int n) { wait_vmcnt_rt<0, 63>(n < 63 ? n : 63); }
 
+// A barrier of the workgroup that waits for the wave's own shared-memory
+// accesses first.  The compiler derives that wait from __syncthreads(), but
+// drops it from a barrier at the head of a loop where only the iteration before
+// left accesses in flight: in the look-ahead forward the waves then passed the
+// barrier with their rows of U still on the way (read in the listing; results
+// that differed between runs once less code stood between the stores and the
+// barrier).  tests/test_barriers.py looks for such barriers in the built code.
+__device__ __forceinline__ void block_sync() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __syncthreads();
+}
+
 // Copies issued per wave when the 64-lane blocks of an NB-block copy are
 // dealt round-robin to NW waves: the wave with the fewest (the last one).
 template <int NB, int NW>

@@ -471,10 +471,10 @@ __global__ __launch_bounds__(512, 2) void k_fwd_la(Shape s, FwdIn in, PrepBufs p
       wait_vmcnt<0>();
     }
     for (int c = 0; c < nc; ++c) {
-      __syncthreads();  // B0
+      block_sync();  // B0
       if (direct(c)) {
-        __syncthreads();  // the row waves' X_c
-        __syncthreads();  // and U_c, from S_c itself
+        block_sync();  // the row waves' X_c
+        block_sync();  // and U_c, from S_c itself
       }
       if (c + 1 < nc) dma_k(c + 1);
       if (c + 2 < nc) dma_a(c + 2);
@@ -504,7 +504,7 @@ __global__ __launch_bounds__(512, 2) void k_fwd_la(Shape s, FwdIn in, PrepBufs p
         for (int i = 0; i < NKT; ++i) S[i] = mma_32(a[i], Uh[pb], S[i]);
 #pragma unroll
         for (int i = 0; i < NKT; ++i) S[i] = mma_32(a[i], Ul[pb], S[i]);
-        if (pb == NT / 2 - 1) __syncthreads();  // B1: the row waves are done with the copy of S_c
+        if (pb == NT / 2 - 1) block_sync();  // B1: the row waves are done with the copy of S_c
       }
       if (c + 1 < nc) put_sop();
       wait_vmcnt<0>();  // the copies issued at the top of the step
@@ -641,7 +641,7 @@ __global__ __launch_bounds__(512, 2) void k_fwd_la(Shape s, FwdIn in, PrepBufs p
       load_tri(mo, OT::M, 0);
     }
     for (int c = 0; c < nc; ++c) {
-      __syncthreads();  // B0: the copy of S_c (and, unless direct, U_c) is there
+      block_sync();  // B0: the copy of S_c (and, unless direct, U_c) is there
       if (direct(c)) {
         if (GDN && rows) {  // X_c = V_c - sum_e diag(a_e) K_c S_c
           Sum ws = zero_sum();
@@ -656,12 +656,12 @@ __global__ __launch_bounds__(512, 2) void k_fwd_la(Shape s, FwdIn in, PrepBufs p
           load_x(c + 1, c);
           load_full(go, OT::G, c + 1);
         }
-        __syncthreads();
+        block_sync();
         if (rows) {
           put_u(form_u(c));
           if constexpr (GDN) load_tri(to, OT::Tu, c + 1);
         }
-        __syncthreads();
+        block_sync();
       }
       const bool more = c + 1 < nc;
       const bool ahead = more && !direct(c + 1);  // X_{c+1}, U_{c+1} are formed in this step
@@ -708,7 +708,7 @@ __global__ __launch_bounds__(512, 2) void k_fwd_la(Shape s, FwdIn in, PrepBufs p
           if (ahead) put_x(c + 1, v_row(c + 1) - (total(ws) + x));
         o += total(os);
       }
-      __syncthreads();  // B1: X_{c+1}; every row wave is done with U_c and the copy of S_c
+      block_sync();  // B1: X_{c+1}; every row wave is done with U_c and the copy of S_c
       if (rows) {
         if (ahead || (!GDN && more)) {
           put_u(form_u(c + 1));
