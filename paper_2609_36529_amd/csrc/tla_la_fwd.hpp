@@ -338,6 +338,14 @@ __global__ __launch_bounds__(la_prep_waves<E>() * 64, E <= 8 ? 4 : 2) void k_pre
 // kept row-major and come back as operands through transposing reads.  (Row
 // tiles of K stacked on Q in 32-row products were slower: 32 lines a load.)
 //
+// With two row tiles (C = 32) a tile has two row waves, one for K's rows (X, U)
+// and one for Q's (outputs): with both sides in one wave and two waves idle an
+// instance took 160-180 registers, one workgroup a CU, and calls of many
+// sequences were slower than before the look-ahead (GDN K64 E8, whole forwards,
+// kernel whose W waits for the update / one wave a tile / two waves a tile: B32
+// H16 T512 268 / 326 / 243 us, B64 H16 T64 93 / 123 / 92 us, B1 H8 T4096 262 /
+// 180 / 155 us; K128 E8 B64 H16 T64 292 / 313 / 261 us).
+//
 // Measured (kernel alone, MI355X, before / after: the kernel whose W waits for
 // the update): GDN B1 H16 T65536 E16 3.85 / 2.90 ms, GDN B1 H16 T777 E8 58 /
 // 36 us, sGLA B4 H8 T4096 E8 177 / 124 us.  A GDN step takes 6.8 k cycles, 5.2 k
@@ -368,7 +376,7 @@ struct LaFwdSmem {
 };
 
 template <int KD, int C, int E, bool PK, bool GDN>
-__global__ __launch_bounds__(512, 2) void k_fwd_la(Shape s, FwdIn in, PrepBufs p, void* out,
+__global__ __launch_bounds__(512, C == 32 ? 4 : 2) void k_fwd_la(Shape s, FwdIn in, PrepBufs p, void* out,
                                                    float* s_final) {
   typedef bf16_t T;
   typedef LaFwdSmem<KD, C, E, PK> Sm;
@@ -376,7 +384,7 @@ __global__ __launch_bounds__(512, 2) void k_fwd_la(Shape s, FwdIn in, PrepBufs p
   constexpr int NT = Sm::NT, NP = Sm::NP, KB = Sm::KB, UE = Sm::UE, SPU = Sm::SPU, E4 = Sm::E4;
   constexpr int VW = PK ? 8 : 16, KT = KD / 32;
   constexpr int NKT = UE * KT / 4;  // state tiles of a state wave
-  static_assert(UE >= 1 && (UE * KT) % 4 == 0 && (NKT <= KT) && NT % 2 == 0 && NT <= 4,
+  static_assert(UE >= 1 && (UE * KT) % 4 == 0 && (NKT <= KT) && (NT == 2 || NT == 4),
                 "one unit per state wave, one row tile per row wave");
   extern __shared__ __align__(16) unsigned char smem_raw[];
   Sm& sm = *reinterpret_cast<Sm*>(smem_raw);
@@ -521,15 +529,15 @@ __global__ __launch_bounds__(512, 2) void k_fwd_la(Shape s, FwdIn in, PrepBufs p
   } else {
     // ================================================= row waves
     if (nc == 0) return;
-    const bool rows = w < NT;  // the wave owns row tile w
-    const int pw = w >> 1;     // last operand of its rows in a triangular matrix
+    const int rt = w & (NT - 1);  // the wave's row tile
+    const int pw = rt >> 1;       // last operand of its rows in a triangular matrix
     if constexpr (!GDN) {
       if (!in.beta)
         for (int r = threadIdx.x - 256; r < 2 * C; r += 256) (&sm.beta[0][0])[r] = 1.f;
     }
     bf16x8 mo[NP][2], go[NP][2], to[NP][2];
     auto load_tri = [&](bf16x8(&x)[NP][2], size_t mat, int c) {
-      const T* src = opsg + (size_t)min(c, nc - 1) * OT::STRIDE + mat + (size_t)OT::tri(w, 0) * 2 * OT::FR + 8 * l;
+      const T* src = opsg + (size_t)min(c, nc - 1) * OT::STRIDE + mat + (size_t)OT::tri(rt, 0) * 2 * OT::FR + 8 * l;
 #pragma unroll
       for (int pp = 0; pp < NP; ++pp)
         if (pp <= pw) {
@@ -538,29 +546,31 @@ __global__ __launch_bounds__(512, 2) void k_fwd_la(Shape s, FwdIn in, PrepBufs p
         }
     };
     auto load_full = [&](bf16x8(&x)[NP][2], size_t mat, int c) {
-      const T* src = opsg + (size_t)min(c, nc - 1) * OT::STRIDE + mat + (size_t)OT::full(w, 0) * 2 * OT::FR + 8 * l;
+      const T* src = opsg + (size_t)min(c, nc - 1) * OT::STRIDE + mat + (size_t)OT::full(rt, 0) * 2 * OT::FR + 8 * l;
 #pragma unroll
       for (int pp = 0; pp < NP; ++pp) {
         x[pp][0] = *(const bf16x8*)(src + (2 * pp) * OT::FR);
         x[pp][1] = *(const bf16x8*)(src + (2 * pp + 1) * OT::FR);
       }
     };
-    // The rows of the state pass: rows 16 w + n of K (chunk ck) and Q (chunk
+    // The rows of the state pass: rows 16 rt + n of K (chunk ck) and Q (chunk
     // cq), 32-key operands.  Chunks are clamped to the last one, rows to the
     // last position (loaded, never used).
     constexpr int NX = KB / 2;
     bf16x8 kf[GDN ? NX : 1], qf[NX];
     auto x_ptr = [&](const void* base, int c) {
-      return (const T*)base + ((tok0 + min(min(c, nc - 1) * C + 16 * w + n, s.T - 1)) * s.H + h) * KD + 8 * g;
+      return (const T*)base + ((tok0 + min(min(c, nc - 1) * C + 16 * rt + n, s.T - 1)) * s.H + h) * KD + 8 * g;
     };
-    auto load_x = [&](int ck, int cq) {
-      const T* kr = x_ptr(in.k, ck);
-      const T* qr = x_ptr(in.q, cq);
+    auto load_k = [&](int c) {
+      const T* kr = x_ptr(in.k, c);
 #pragma unroll
-      for (int k = 0; k < NX; ++k) {
-        qf[k] = *(const bf16x8*)(qr + 32 * k);
+      for (int k = 0; k < NX; ++k)
         if constexpr (GDN) kf[k] = *(const bf16x8*)(kr + 32 * k);
-      }
+    };
+    auto load_q = [&](int c) {
+      const T* qr = x_ptr(in.q, c);
+#pragma unroll
+      for (int k = 0; k < NX; ++k) qf[k] = *(const bf16x8*)(qr + 32 * k);
     };
     // block k (32 keys) of half unit u (16 columns: one slice, or with PK two)
     auto s_op = [&](int u, int k) {
@@ -578,7 +588,7 @@ __global__ __launch_bounds__(512, 2) void k_fwd_la(Shape s, FwdIn in, PrepBufs p
       acc = mma_16(bl, a[0], acc);
       acc = mma_16(bh, a[1], acc);
     };
-    const int row = 16 * w + n;  // this lane's row of a chunk
+    const int row = 16 * rt + n;  // this lane's row of a chunk
     // four values of the lane's row as a (hi, lo) row-major tile
     auto put_rows = [&](bf16_t(*dst)[C][16], f32x4 x) {
       bf16x4 hi, lo;
@@ -635,94 +645,107 @@ __global__ __launch_bounds__(512, 2) void k_fwd_la(Shape s, FwdIn in, PrepBufs p
       }
     };
 
-    if (rows) {
-      load_x(0, 0);
-      if constexpr (GDN) load_tri(to, OT::Tu, 0);
-      load_tri(mo, OT::M, 0);
-    }
-    for (int c = 0; c < nc; ++c) {
-      block_sync();  // B0: the copy of S_c (and, unless direct, U_c) is there
-      if (direct(c)) {
-        if (GDN && rows) {  // X_c = V_c - sum_e diag(a_e) K_c S_c
-          Sum ws = zero_sum();
+    // The row waves' steps: KS forms X and U of the row tile, QS its outputs.
+    auto run = [&](auto ks_c, auto qs_c) {
+      constexpr bool KS = decltype(ks_c)::value, QS = decltype(qs_c)::value;
+      if constexpr (KS && GDN) load_k(0);
+      if constexpr (QS) load_q(0);
+      if constexpr (KS && GDN) load_tri(to, OT::Tu, 0);
+      if constexpr (QS) load_tri(mo, OT::M, 0);
+      for (int c = 0; c < nc; ++c) {
+        block_sync();  // B0: the copy of S_c (and, unless direct, U_c) is there
+        if (direct(c)) {
+          if constexpr (KS && GDN) {  // X_c = V_c - sum_e diag(a_e) K_c S_c
+            Sum ws = zero_sum();
+#pragma unroll
+            for (int u = 0; u < 2 * UE; ++u) {
+              f32x4 P = zero4();
+#pragma unroll
+              for (int k = 0; k < NX; ++k) P = mma_16(s_op(u, k), kf[k], P);
+              ws.p[u % NS] += sm.ca[c & 1][cslc(u)][row] * P;
+            }
+            put_x(c, v_row(c) - total(ws));
+            load_k(c + 1);  // (Q_c is there)
+            load_full(go, OT::G, c + 1);
+          }
+          block_sync();
+          if constexpr (KS) {
+            put_u(form_u(c));
+            if constexpr (GDN) load_tri(to, OT::Tu, c + 1);
+          }
+          block_sync();
+        }
+        const bool more = c + 1 < nc;
+        const bool ahead = more && !direct(c + 1);  // X_{c+1}, U_{c+1} are formed in this step
+        constexpr bool DK = KS && GDN;
+        f32x4 o = zero4(), x = zero4();
+        if constexpr (DK || QS) {
+#pragma unroll
+          for (int pp = 0; pp < NP; ++pp) {
+            const bf16x8 uh = row_op(sm.Uo[0], pp), ul = row_op(sm.Uo[1], pp);
+            if constexpr (DK) mma3(x, go[pp], uh, ul);
+            if (QS && pp <= pw) mma3(o, mo[pp], uh, ul);
+          }
+          if constexpr (QS) load_tri(mo, OT::M, c + 1);
+          if constexpr (DK) load_full(go, OT::G, c + 2);
+          // K_{c+1} S_c and Q_c S_c, all half units, one pass over the copy of S_c
+          f32x4 Pk[DK ? 2 * UE : 1], Pq[QS ? 2 * UE : 1];
 #pragma unroll
           for (int u = 0; u < 2 * UE; ++u) {
-            f32x4 P = zero4();
-#pragma unroll
-            for (int k = 0; k < NX; ++k) P = mma_16(s_op(u, k), kf[k], P);
-            ws.p[u % NS] += sm.ca[c & 1][cslc(u)][row] * P;
+            if constexpr (QS) Pq[u] = zero4();
+            if constexpr (DK) Pk[u] = zero4();
           }
-          put_x(c, v_row(c) - total(ws));
-          load_x(c + 1, c);
-          load_full(go, OT::G, c + 1);
-        }
-        block_sync();
-        if (rows) {
-          put_u(form_u(c));
-          if constexpr (GDN) load_tri(to, OT::Tu, c + 1);
-        }
-        block_sync();
-      }
-      const bool more = c + 1 < nc;
-      const bool ahead = more && !direct(c + 1);  // X_{c+1}, U_{c+1} are formed in this step
-      f32x4 o = zero4();
-      if (rows) {
-        f32x4 x = zero4();
+          const T* kr = x_ptr(in.k, ahead ? c + 2 : c + 1);
+          const T* qr = x_ptr(in.q, c + 1);
 #pragma unroll
-        for (int pp = 0; pp < NP; ++pp) {
-          const bf16x8 uh = row_op(sm.Uo[0], pp), ul = row_op(sm.Uo[1], pp);
-          if constexpr (GDN) mma3(x, go[pp], uh, ul);
-          if (pp <= pw) mma3(o, mo[pp], uh, ul);
-        }
-        load_tri(mo, OT::M, c + 1);
-        if constexpr (GDN) load_full(go, OT::G, c + 2);
-        // K_{c+1} S_c and Q_c S_c, all half units, one pass over the copy of S_c
-        f32x4 PK_[GDN ? 2 * UE : 1], PQ[2 * UE];
+          for (int k = 0; k < NX; ++k) {
 #pragma unroll
-        for (int u = 0; u < 2 * UE; ++u) {
-          PQ[u] = zero4();
-          if constexpr (GDN) PK_[u] = zero4();
-        }
-        const T* kr = x_ptr(in.k, ahead ? c + 2 : c + 1);
-        const T* qr = x_ptr(in.q, c + 1);
-#pragma unroll
-        for (int k = 0; k < NX; ++k) {
+            for (int u = 0; u < 2 * UE; ++u) {
+              const bf16x8 sb = s_op(u, k);
+              if constexpr (QS) Pq[u] = mma_16(sb, qf[k], Pq[u]);
+              if constexpr (DK) Pk[u] = mma_16(sb, kf[k], Pk[u]);
+            }
+            // done with this key block: the next step's rows
+            if constexpr (QS) qf[k] = *(const bf16x8*)(qr + 32 * k);
+            if constexpr (DK) kf[k] = *(const bf16x8*)(kr + 32 * k);
+          }
+          Sum os = zero_sum(), ws = zero_sum();
 #pragma unroll
           for (int u = 0; u < 2 * UE; ++u) {
-            const bf16x8 sb = s_op(u, k);
-            PQ[u] = mma_16(sb, qf[k], PQ[u]);
-            if constexpr (GDN) PK_[u] = mma_16(sb, kf[k], PK_[u]);
+            const int e = cslc(u);
+            if constexpr (QS) os.p[u % NS] += sm.cbc[c & 1][0][e][row] * Pq[u];
+            if constexpr (DK) ws.p[u % NS] += (sm.gC[c & 1][e] * sm.ca[(c + 1) & 1][e][row]) * Pk[u];
           }
-          // done with this key block: the next step's rows
-          qf[k] = *(const bf16x8*)(qr + 32 * k);
-          if constexpr (GDN) kf[k] = *(const bf16x8*)(kr + 32 * k);
+          if constexpr (DK)
+            if (ahead) put_x(c + 1, v_row(c + 1) - (total(ws) + x));
+          if constexpr (QS) o += total(os);
         }
-        Sum os = zero_sum(), ws = zero_sum();
-#pragma unroll
-        for (int u = 0; u < 2 * UE; ++u) {
-          const int e = cslc(u);
-          os.p[u % NS] += sm.cbc[c & 1][0][e][row] * PQ[u];
-          if constexpr (GDN) ws.p[u % NS] += (sm.gC[c & 1][e] * sm.ca[(c + 1) & 1][e][row]) * PK_[u];
+        block_sync();  // B1: X_{c+1}; every row wave is done with U_c and the copy of S_c
+        if constexpr (KS) {
+          if (ahead || (!GDN && more)) {
+            put_u(form_u(c + 1));
+            if constexpr (GDN) load_tri(to, OT::Tu, c + 2);
+          }
         }
-        if constexpr (GDN)
-          if (ahead) put_x(c + 1, v_row(c + 1) - (total(ws) + x));
-        o += total(os);
-      }
-      block_sync();  // B1: X_{c+1}; every row wave is done with U_c and the copy of S_c
-      if (rows) {
-        if (ahead || (!GDN && more)) {
-          put_u(form_u(c + 1));
-          if constexpr (GDN) load_tri(to, OT::Tu, c + 2);
-        }
-        const int t = c * C + row;
-        if (t < s.T && (!PK || g < 2)) {
-          const size_t off = ((tok0 + t) * s.H + h) * (size_t)V + v0 + 4 * g;
-          if (s.out_bf16)
-            __builtin_nontemporal_store(__builtin_bit_cast(u32x2, cvt_frag<T>(o)), (u32x2*)((T*)out + off));
-          else
-            __builtin_nontemporal_store(__builtin_bit_cast(u32x4, o), (u32x4*)((float*)out + off));
+        if constexpr (QS) {
+          const int t = c * C + row;
+          if (t < s.T && (!PK || g < 2)) {
+            const size_t off = ((tok0 + t) * s.H + h) * (size_t)V + v0 + 4 * g;
+            if (s.out_bf16)
+              __builtin_nontemporal_store(__builtin_bit_cast(u32x2, cvt_frag<T>(o)), (u32x2*)((T*)out + off));
+            else
+              __builtin_nontemporal_store(__builtin_bit_cast(u32x4, o), (u32x4*)((float*)out + off));
+          }
         }
       }
+    };
+    if constexpr (NT == 4) {
+      run(std::true_type{}, std::true_type{});
+    } else {  // two waves a row tile, one side each
+      if (w < NT)
+        run(std::false_type{}, std::true_type{});
+      else
+        run(std::true_type{}, std::false_type{});
     }
   }
 }
