@@ -323,6 +323,7 @@ __global__ __launch_bounds__(la_prep_waves<E>() * 64, E <= 8 ? 4 : 2) void k_pre
 // U_{c+1} = Tu X, and store the outputs.  Two barriers a step:
 //   B0 .. B1  state: the update's first half   row: O_c, X_{c+1}
 //   B1 .. B0  state: second half, copy of S    row: U_{c+1}, stores
+// (GDN's last step has no B1: nothing is written to shared memory after it.)
 // A row tile's partial sums over slices stay in registers (no exchange), and
 // the row waves read K, Q, M, G and Tu straight from global memory into
 // registers, each a whole step ahead, in operand order.
@@ -512,7 +513,8 @@ __global__ __launch_bounds__(512, C == 32 ? 4 : 2) void k_fwd_la(Shape s, FwdIn 
         for (int i = 0; i < NKT; ++i) S[i] = mma_32(a[i], Uh[pb], S[i]);
 #pragma unroll
         for (int i = 0; i < NKT; ++i) S[i] = mma_32(a[i], Ul[pb], S[i]);
-        if (pb == NT / 2 - 1) block_sync();  // B1: the row waves are done with the copy of S_c
+        // B1: the row waves are done with the copy of S_c
+        if (pb == NT / 2 - 1 && (!GDN || c + 1 < nc)) block_sync();
       }
       if (c + 1 < nc) put_sop();
       wait_vmcnt<0>();  // the copies issued at the top of the step
@@ -652,7 +654,15 @@ __global__ __launch_bounds__(512, C == 32 ? 4 : 2) void k_fwd_la(Shape s, FwdIn 
       if constexpr (QS) load_q(0);
       if constexpr (KS && GDN) load_tri(to, OT::Tu, 0);
       if constexpr (QS) load_tri(mo, OT::M, 0);
-      for (int c = 0; c < nc; ++c) {
+      // One step.  GDN: the last chunk's (LAST), which forms nothing of a next
+      // chunk, is a copy of its own.  Done like the others it cost calls of many
+      // short sequences a third product and the wait for rows never used (whole
+      // forwards, B64 H16 T64 K128, before the look-ahead / with that / now: E8
+      // 256 / 290 / 260 us, E4 183 / 216 / 183, E16 549 / 593 / 535); skipped by a
+      // branch inside the loop's step, the loads in flight have to arrive at every
+      // join (10-30% slower at all lengths).
+      auto step = [&](auto last_c, int c) {
+        constexpr bool LAST = decltype(last_c)::value;
         block_sync();  // B0: the copy of S_c (and, unless direct, U_c) is there
         if (direct(c)) {
           if constexpr (KS && GDN) {  // X_c = V_c - sum_e diag(a_e) K_c S_c
@@ -665,19 +675,21 @@ __global__ __launch_bounds__(512, C == 32 ? 4 : 2) void k_fwd_la(Shape s, FwdIn 
               ws.p[u % NS] += sm.ca[c & 1][cslc(u)][row] * P;
             }
             put_x(c, v_row(c) - total(ws));
-            load_k(c + 1);  // (Q_c is there)
-            load_full(go, OT::G, c + 1);
+            if constexpr (!LAST) {
+              load_k(c + 1);  // (Q_c is there)
+              load_full(go, OT::G, c + 1);
+            }
           }
           block_sync();
           if constexpr (KS) {
             put_u(form_u(c));
-            if constexpr (GDN) load_tri(to, OT::Tu, c + 1);
+            if constexpr (GDN && !LAST) load_tri(to, OT::Tu, c + 1);
           }
           block_sync();
         }
-        const bool more = c + 1 < nc;
+        const bool more = GDN ? !LAST : c + 1 < nc;
         const bool ahead = more && !direct(c + 1);  // X_{c+1}, U_{c+1} are formed in this step
-        constexpr bool DK = KS && GDN;
+        constexpr bool DK = KS && GDN && !LAST;
         f32x4 o = zero4(), x = zero4();
         if constexpr (DK || QS) {
 #pragma unroll
@@ -686,7 +698,7 @@ __global__ __launch_bounds__(512, C == 32 ? 4 : 2) void k_fwd_la(Shape s, FwdIn 
             if constexpr (DK) mma3(x, go[pp], uh, ul);
             if (QS && pp <= pw) mma3(o, mo[pp], uh, ul);
           }
-          if constexpr (QS) load_tri(mo, OT::M, c + 1);
+          if constexpr (QS && !LAST) load_tri(mo, OT::M, c + 1);
           if constexpr (DK) load_full(go, OT::G, c + 2);
           // K_{c+1} S_c and Q_c S_c, all half units, one pass over the copy of S_c
           f32x4 Pk[DK ? 2 * UE : 1], Pq[QS ? 2 * UE : 1];
@@ -706,7 +718,7 @@ __global__ __launch_bounds__(512, C == 32 ? 4 : 2) void k_fwd_la(Shape s, FwdIn 
               if constexpr (DK) Pk[u] = mma_16(sb, kf[k], Pk[u]);
             }
             // done with this key block: the next step's rows
-            if constexpr (QS) qf[k] = *(const bf16x8*)(qr + 32 * k);
+            if constexpr (QS && !LAST) qf[k] = *(const bf16x8*)(qr + 32 * k);
             if constexpr (DK) kf[k] = *(const bf16x8*)(kr + 32 * k);
           }
           Sum os = zero_sum(), ws = zero_sum();
@@ -720,7 +732,7 @@ __global__ __launch_bounds__(512, C == 32 ? 4 : 2) void k_fwd_la(Shape s, FwdIn 
             if (ahead) put_x(c + 1, v_row(c + 1) - (total(ws) + x));
           if constexpr (QS) o += total(os);
         }
-        block_sync();  // B1: X_{c+1}; every row wave is done with U_c and the copy of S_c
+        if constexpr (!LAST) block_sync();  // B1: X_{c+1}; every row wave is done with U_c and the copy of S_c
         if constexpr (KS) {
           if (ahead || (!GDN && more)) {
             put_u(form_u(c + 1));
@@ -737,7 +749,9 @@ __global__ __launch_bounds__(512, C == 32 ? 4 : 2) void k_fwd_la(Shape s, FwdIn 
               __builtin_nontemporal_store(__builtin_bit_cast(u32x4, o), (u32x4*)((float*)out + off));
           }
         }
-      }
+      };
+      for (int c = 0; c < nc - GDN; ++c) step(std::false_type{}, c);
+      if constexpr (GDN) step(std::true_type{}, nc - 1);
     };
     if constexpr (NT == 4) {
       run(std::true_type{}, std::true_type{});
