@@ -91,6 +91,18 @@ template <int E> constexpr int bwd_waves() { return E >= 8 ? 8 : 4; }
 // The reverse recurrence with two slices a tile (PK, see k_bwd_rec).
 template <typename T, int KD, int C, int E>
 constexpr bool rec_pk() { return sizeof(T) == 2 && E == 16 && KD >= 64; }
+// Whether a call takes it.  K = 128: always.  K = 64 without a final-state
+// gradient: only while its 16-column workgroups would leave half of the CUs
+// idle; past that the C x C products, which every 8-column workgroup repeats,
+// cost more than the second slice (whole backwards, GDN V64, 16 / 8 columns: B1
+// H8 T4096 528 / 426 us, B2 H16 T2048 499 / 439, but B4 H16 T4096 1539 / 1685,
+// B64 H16 T64 465 / 532).  With a final-state gradient 8 columns are faster at
+// all sizes (B1 H8 T4096 771 / 446, B64 H16 T64 658 / 619).  Both give the same
+// bits, so that the heads of a call do not reach a sequence's gradients.
+template <typename T, int KD, int C, int E>
+inline bool rec_halves(const Shape& s, const BwdBufs& bb) {
+  return rec_pk<T, KD, C, E>() && (KD == 128 || bb.dSck_lo || s.NH * (s.V / 16) <= 128);
+}
 
 // ============================================================ reverse recurrence
 template <typename T, int KD, int C, int E, int NW>
@@ -488,7 +500,15 @@ __global__ __launch_bounds__(NW * 64) void k_bwd_rec(Shape s, FwdIn in, const vo
 #pragma unroll
       for (int i = 0; i < SPW; ++i) {
         const int u = w * SPW + i;
-        if (!RAGGED || u < UE) acc += *(const f32x4*)&sm.coef[2][slc(u)][16 * rt + 4 * g] * z[i];
+        if constexpr (rec_pk<T, KD, C, E>()) {
+          // products rounded by themselves, as the sum over column halves below
+          // takes them: the same bits with and without PK
+#pragma clang fp contract(off)
+          const f32x4 x = *(const f32x4*)&sm.coef[2][slc(u)][16 * rt + 4 * g] * z[i];
+          acc = i ? acc + x : x;
+        } else {
+          if (!RAGGED || u < UE) acc += *(const f32x4*)&sm.coef[2][slc(u)][16 * rt + 4 * g] * z[i];
+        }
       }
       if constexpr (PK) {  // both slices of the unit
 #pragma unroll
@@ -708,7 +728,7 @@ struct StateSmem {
 // 142 us; a run-time branch in one kernel spilled 140 registers).
 template <typename T, int KD, int C, int E, bool PDS, bool GDN>
 __global__ __launch_bounds__(STATE_NTHR) void k_bwd_state(Shape s, FwdIn in, const void* dOv,
-                                                          PrepBufs p, SavedBufs sv, BwdBufs bb) {
+                                                          PrepBufs p, SavedBufs sv, BwdBufs bb, int halves) {
   constexpr int NT = C / 16;
   constexpr int KT = KD / 16;
   constexpr int CTW = (KT + 3) / 4;      // key column tiles per wave
@@ -856,17 +876,16 @@ __global__ __launch_bounds__(STATE_NTHR) void k_bwd_state(Shape s, FwdIn in, con
   const T* dSck = (const T*)bb.dSck;
   const T* dSlk = (const T*)bb.dSck_lo;
   Raw8<T> sbuf[CTW][NPMAX], dbuf[CTW][NPMAX], dlbuf[PDS ? CTW : 1][PDS ? NPMAX : 1];
-  // dS' of the 8-column recurrence keeps the two column halves of a 16 x 16
-  // block one after the other
-  constexpr bool HALF = rec_pk<T, KD, C, E>();
-  const int lnD = 8 * n + 128 * (g & 1) - (16 * n + 8 * (g & 1));  // this lane's piece against Sck's order
+  // dS' of the 8-column recurrence (halves) keeps the two column halves of a
+  // 16 x 16 block one after the other: this lane's piece against Sck's order
+  const int lnD = rec_pk<T, KD, C, E>() && halves ? 8 * n + 128 * (g & 1) - (16 * n + 8 * (g & 1)) : 0;
   auto load_pair = [&](int e, int c, int pp) {
     const int ct = min(q * CTW + c, KT - 1);
     const int vb = min(2 * pp + (g >> 1), VB - 1);
     const size_t off = ((((size_t)ch * E + e) * VB + vb) * KD + 16 * ct + n) * 16 + 8 * (g & 1);
     sbuf[c][pp] = load8(Sck + off);
-    dbuf[c][pp] = load8(dSck + off + (HALF ? lnD : 0));
-    if constexpr (PDS) dlbuf[c][pp] = load8(dSlk + off + (HALF ? lnD : 0));
+    dbuf[c][pp] = load8(dSck + off + lnD);
+    if constexpr (PDS) dlbuf[c][pp] = load8(dSlk + off + lnD);
   };
 #pragma unroll
   for (int pp = 0; pp < NPMAX; ++pp)
@@ -1882,10 +1901,9 @@ template <typename T, int KD, int C, int E>
 static hipError_t rec_inst(const Shape& s, const FwdIn& in, const void* dO, const float* dSf,
                            const PrepBufs& p, const BwdBufs& bb, float* ds0, hipStream_t st) {
   constexpr int NW = bwd_waves<E>();
-  constexpr bool PK = rec_pk<T, KD, C, E>();
   const size_t smem = sizeof(RecSmem<T, KD, C, E, NW>);
-  auto go = [&](auto pds_c) {
-    constexpr bool PDS = decltype(pds_c)::value;
+  auto go = [&](auto pds_c, auto pk_c) {
+    constexpr bool PDS = decltype(pds_c)::value, PK = decltype(pk_c)::value;
     static bool attr = false;
     if (!attr) {
       (void)hipFuncSetAttribute((const void*)k_bwd_rec<T, KD, C, E, NW, PDS, PK>,
@@ -1896,8 +1914,11 @@ static hipError_t rec_inst(const Shape& s, const FwdIn& in, const void* dO, cons
                        smem, st, s, in, dO, dSf, p, bb, ds0);
     return hipGetLastError();
   };
-  if (sizeof(T) == 2 && bb.dSck_lo) return go(std::integral_constant<bool, sizeof(T) == 2>{});
-  return go(std::integral_constant<bool, false>{});
+  constexpr std::integral_constant<bool, rec_pk<T, KD, C, E>()> pk;
+  if (sizeof(T) == 2 && bb.dSck_lo) return go(std::integral_constant<bool, sizeof(T) == 2>{}, pk);
+  if constexpr (pk && KD < 128)
+    if (!rec_halves<T, KD, C, E>(s, bb)) return go(std::false_type{}, std::false_type{});
+  return go(std::false_type{}, pk);
 }
 
 template <typename T, int KD, int C, int E>
@@ -1913,7 +1934,7 @@ static hipError_t state_inst(const Shape& s, const FwdIn& in, const void* dO, co
       attr = true;
     }
     hipLaunchKernelGGL((k_bwd_state<T, KD, C, E, PDS, GDN>), dim3(s.NH * s.Nc), dim3(STATE_NTHR), smem,
-                       st, s, in, dO, p, sv, bb);
+                       st, s, in, dO, p, sv, bb, (int)rec_halves<T, KD, C, E>(s, bb));
     return hipGetLastError();
   };
   auto pick = [&](auto pds_c) {

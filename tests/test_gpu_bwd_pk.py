@@ -39,3 +39,25 @@ def test_backward(variant, final, K, C, E, V):
         err = rel_err(host64(gr[key]), ref[key])
         print(f"{variant=} {final=} {K=} {E=} {V=} {key}: {err:.2e}", flush=True)
         assert err <= 2e-2, (key, err)
+
+
+@pytest.mark.parametrize("variant", [0, 1])
+def test_widths_agree(variant):
+    """K = 64 without a final-state gradient takes 8-column workgroups for few
+    heads and 16-column ones for many: the gradients of a sequence have the same
+    bits alone and among others."""
+    K, C, E, V, H, B, T = 64, 64, 16, 64, 8, 5, 139
+    cfg = synth.Config("pk", variant, B, T, H, K, V, E, C, "bf16", "softplus16", variant == 1, 0.02, 37)
+    assert B * H * V // 16 > 128 >= H * V // 16  # the two sides of the rule
+    inp = synth.make_inputs(cfg)
+    inp["dO"] = synth.make_dO(cfg, seed=5)
+    got = []
+    for pick in (slice(0, B), slice(1, 2)):
+        d = {k: (None if v is None else v[pick].contiguous().to("cuda")) for k, v in inp.items()}
+        args = (d["q"], d["k"], d["v"], d["q2"], d["k2"], d["g"], d["beta"], d["s0"])
+        _, _, saved = tla.fwd(variant, *args, chunk=C, training=True)
+        got.append(tla.bwd(variant, *args, d["dO"], saved, chunk=C, out_dtype=torch.float32))
+    torch.cuda.synchronize()
+    for key, x in got[0].items():
+        if x is not None:
+            assert torch.equal(x[1:2], got[1][key]), key
