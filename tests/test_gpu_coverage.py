@@ -165,7 +165,7 @@ def test_autograd_wrapper_matches_bwd(variant):
 @pytest.mark.parametrize("V,T,s0", [(128, 150, 0.02), (64, 77, 0.0), (256, 200, 0.02)])
 def test_e16_inference_forward(variant, V, T, s0):
     """E = 16, K = 128, chunk 64 with bf16 operands: the inference forward
-    (two key slices per accumulator tile, 8 value columns per workgroup) and
+    (four key slices per accumulator tile, 8 value columns per workgroup) and
     the training forward (16 columns per workgroup) against the oracle."""
     cfg = cfg_of(variant, "bf16", B=1, T=T, H=3, K=128, V=V, E=16, chunk=64, s0=s0, seed=23)
     inp = synth.make_inputs(cfg)

@@ -1,9 +1,10 @@
-"""The look-ahead forward (bf16 operands, K >= 64) at the edges of its dispatch:
-lengths around a chunk and around the chunks that form W from their own start
-state (every 16th), both workgroup widths (16 value columns, and 8 where those
-would leave half of the chip idle), both variants, against the fp64 oracle.
-Bound: the bf16 parity bound of the other forward tests (max|err| / RMS 2e-2,
-one bf16 rounding of the state operand per chunk)."""
+"""The look-ahead forward (bf16 operands, K >= 64, E >= 4) at the edges of its
+dispatch: lengths around a chunk and around the chunks that form W from their own
+start state (every 16th), both workgroup widths (16 value columns, and 8 where
+those would leave half of the chip idle), both variants, extreme gates, against
+the fp64 oracle; the two widths bit for bit; sequences cut and resumed.  Bound
+against the oracle: the bf16 parity bound of the other forward tests (max|err| /
+RMS 2e-2, one bf16 rounding of the state operand per chunk)."""
 import numpy as np
 import pytest
 import torch
@@ -11,7 +12,7 @@ import torch
 import oracle
 import paper_2609_36529_amd as tla
 from paper_2609_36529_amd import synth
-from helpers import host64, rel_err
+from helpers import host64, oracle_fwd_heads, rel_err
 
 pytestmark = pytest.mark.gpu
 TOL = 2e-2
@@ -47,6 +48,46 @@ def test_lengths(variant, K, C, E, V, T):
 
 
 @pytest.mark.parametrize("variant", [0, 1])
+@pytest.mark.parametrize("K,C,E,V", [(128, 64, 8, 128), (128, 64, 4, 48), (128, 32, 8, 128), (64, 32, 8, 64)])
+@pytest.mark.parametrize("chunks,tail", [(0, 1), (1, 0), (17, 5)])
+def test_many_heads(variant, K, C, E, V, chunks, tail):
+    """The 16-column workgroups against the oracle on the first and the last
+    head: one position, one whole chunk, and past the chunk that forms its W from
+    its own start state."""
+    T, H = chunks * C + tail, 8
+    B = 128 // (H * V // 16) + 1
+    assert B * H * V // 16 > 128
+    inp = _inputs(variant, B, T, H, K, V, E, C)
+    o, sf = _fwd(variant, inp, C)
+    assert torch.isfinite(o).all() and torch.isfinite(sf).all()
+    for (b, h), (ro, rs) in oracle_fwd_heads(variant, inp, [(0, 0), (B - 1, H - 1)]).items():
+        eo, es = rel_err(host64(o[b, :, h]), ro), rel_err(host64(sf[b, h]), rs)
+        print(f"{variant=} {K=} {C=} {E=} {V=} {T=} head {(b, h)}: o {eo:.2e} s_final {es:.2e}", flush=True)
+        assert eo <= TOL and es <= TOL
+
+
+@pytest.mark.parametrize("variant", [0, 1])
+@pytest.mark.parametrize("K,C,E", [(128, 64, 8), (128, 64, 16), (64, 32, 8)])
+def test_extreme_gates(variant, K, C, E):
+    """Log-gates of -1000 and log(2^-5) per token, inside a chunk, on its last
+    position and on the first of the next: the tile factors exp(G_r - G_m),
+    exp(G_m - G_c) and the cross-chunk decays stay finite and match the oracle."""
+    inp = _inputs(variant, 1, 3 * C + 22, 2, K, 64, E, C)
+    g = inp["g"].clone()
+    g[:, ::5] = -1000.0
+    g[:, 1::5] = float(np.log(2.0 ** -5))
+    g[:, C - 1] = g[:, 2 * C] = -1000.0
+    inp["g"] = g
+    o, sf = _fwd(variant, inp, C)
+    ro, rs = oracle.fwd(variant, *[synth.to64(inp[n]) for n in ("q", "k", "v", "q2", "k2", "g")],
+                        synth.to64(inp["beta"]), synth.to64(inp["s0"]))
+    eo, es = rel_err(host64(o), ro), rel_err(host64(sf), rs)
+    print(f"{variant=} {K=} {C=} {E=}: o {eo:.2e} s_final {es:.2e}", flush=True)
+    assert np.all(np.isfinite(host64(o))) and np.all(np.isfinite(host64(sf)))
+    assert eo <= TOL and es <= TOL
+
+
+@pytest.mark.parametrize("variant", [0, 1])
 @pytest.mark.parametrize("K,C,E", [(128, 64, 8), (128, 64, 4), (128, 32, 8), (64, 32, 8)])
 def test_widths_agree(variant, K, C, E):
     """The 8-column workgroups (few heads) and the 16-column ones run the same
@@ -75,3 +116,24 @@ def test_resume_at_sync(C):
     o2, sf2 = _fwd(1, rest, C, s0=mid)
     assert torch.equal(o[:, T:], o2) and torch.equal(sf, sf2)
     assert np.all(np.isfinite(host64(o)))
+
+
+@pytest.mark.parametrize("variant", [0, 1])
+@pytest.mark.parametrize("E", [8, 16])
+def test_resume_elsewhere(variant, E):
+    """Cut at another chunk boundary (8 chunks of 64): sGLA, whose U needs no
+    state, repeats the uncut sequence bit for bit; GDN forms the W of the first
+    chunk from the bf16 operands of another state (that chunk's own start instead
+    of the one before), each element of which is within 2^-9 of the fp32 state:
+    operands at most 2^-8 apart, and so the results in the 2-norm (measured 4e-5)."""
+    C, cut = 64, 512
+    inp = _inputs(variant, 1, cut + 300, 4, 128, 128, E, C)
+    o, sf = _fwd(variant, inp, C)
+    parts = [{k: (v if v is None or k == "s0" else v[:, sl].contiguous()) for k, v in inp.items()}
+             for sl in (slice(0, cut), slice(cut, None))]
+    _, mid = _fwd(variant, parts[0], C)
+    o2, sf2 = _fwd(variant, parts[1], C, s0=mid)
+    for x, y in ((o[:, cut:], o2), (sf, sf2)):
+        d = ((x.double() - y.double()).norm() / x.double().norm()).item()
+        print(f"{variant=} {E=}: {d:.2e}", flush=True)
+        assert d <= (2.0 ** -8 if variant == 1 else 0.0)

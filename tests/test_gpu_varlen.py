@@ -2,8 +2,9 @@
 tla_bwd_varlen): every packed sequence must give what the fp64 oracle gives
 for that sequence alone, from its own initial state (the state restarts with
 each sequence), including empty sequences, ragged last chunks and sequences
-of several chunks; and a packed batch of equal lengths must reproduce the
-fixed-length entry points bit for bit."""
+of several chunks, in training and in inference; a packed batch of equal lengths
+must reproduce the fixed-length entry points bit for bit, and in inference every
+packed sequence the call with that sequence alone."""
 import dataclasses
 
 import numpy as np
@@ -141,3 +142,40 @@ def test_varlen_all_empty_passes_states_through():
                        out_dtype=torch.float32, cu_seqlens=dev(cu), max_seqlen=1)
     torch.cuda.synchronize()
     assert torch.equal(sf.cpu(), s0)
+
+
+# inference: an empty and a one-token sequence, ragged and whole chunks, and one
+# longer than 17 chunks of 64
+LONG = [150, 0, 1, 64, 37, 1093, 128]
+
+
+@pytest.mark.parametrize("variant", [SGLA, GDN])
+@pytest.mark.parametrize("K,chunk,E,H,V", [(128, 64, 8, 2, 128), (128, 64, 8, 4, 128), (128, 64, 4, 2, 64),
+                                           (128, 64, 16, 2, 48), (128, 32, 8, 4, 128), (64, 32, 8, 6, 64)])
+def test_varlen_inference(variant, K, chunk, E, H, V):
+    """The inference forward over packed sequences (7 of them: 8 value columns a
+    workgroup up to 128 / (7 V / 16) heads, 16 beyond; E = 16 always 8) against the
+    oracle, and bit for bit against each sequence alone, which takes 8 columns."""
+    cfg, inp, s0, _, _, cu = packed_case(variant, "bf16", LONG, chunk=chunk, H=H, K=K, V=V, E=E)
+    d = {k: dev(v) for k, v in inp.items()}
+    args = ("q", "k", "v", "q2", "k2", "g", "beta")
+    s0d = dev(s0)
+    o, sf, _ = tla.fwd(variant, *[d[n] for n in args], s0d, chunk=chunk, out_dtype=torch.float32,
+                       cu_seqlens=dev(cu), max_seqlen=max(LONG))
+    torch.cuda.synchronize()
+    assert torch.isfinite(o).all() and torch.isfinite(sf).all()
+    for i in range(len(LONG)):
+        a, b = int(cu[i]), int(cu[i + 1])
+        if a == b:
+            assert torch.equal(sf[i], s0d[i])
+            continue
+        one = [None if d[n] is None else d[n][:, a:b].clone() for n in args]  # (aligned)
+        o1, sf1, _ = tla.fwd(variant, *one, s0d[i:i + 1].clone(), chunk=chunk, out_dtype=torch.float32)
+        torch.cuda.synchronize()
+        assert torch.equal(o[:, a:b], o1) and torch.equal(sf[i:i + 1], sf1), i
+        ro, rs = oracle.fwd(variant, *[seq_slice(inp[nm], a, b) for nm in NAMES],
+                            seq_slice(inp["beta"], a, b), synth.to64(s0[i:i + 1]))
+        eo, es = rel_err(host64(o1), ro), rel_err(host64(sf1), rs)
+        print(f"varlen inference {variant=} {K=} {chunk=} {E=} {H=} T={b - a}: o {eo:.1e} s_final {es:.1e}",
+              flush=True)
+        assert eo <= TOL_BF16 and es <= TOL_BF16, (i, eo, es)
