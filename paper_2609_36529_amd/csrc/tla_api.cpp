@@ -329,8 +329,8 @@ static int fwd_impl(const tla_desc* d, const int32_t* cu, long long total, const
   const tla::PrepBufs pb =
       saved ? prep_bufs(L, (char*)saved + L.sv_prep, true) : prep_bufs(L, ws, false);
   hipError_t e;
-  // inference with bf16 operands and K >= 64: the look-ahead recurrence
-  const bool la = !saved && tla::la_instance(s.K, s.C, s.E, s.in_bf16);
+  // inference with bf16 operands, K >= 64 and E >= 4: the look-ahead recurrence
+  const bool la = !saved && tla::la_instance(s);
   if (ntok > 0) {
     e = timed(PROF_PREP, st, [&] {
       return la ? tla::launch_prep_la(s, in, pb, st) : tla::launch_prep(s, in, pb, st);

@@ -293,7 +293,7 @@ struct RecStage {
 // last chunks far larger than elsewhere in the sequence, and one bf16
 // rounding of it would then dominate the gradients of those chunks.
 //
-// PK (bf16, E = 16): an accumulator tile holds two key slices side by side, 8
+// PK (bf16, E = 16, K >= 64; see rec_halves): an accumulator tile holds two key slices side by side, 8
 // value columns each (columns 0..7 slice 2 u, 8..15 slice 2 u + 1 of "unit" u),
 // so that a wave owns one unit with the registers and the shared memory of the
 // E = 8 instance: its inputs come a chunk ahead again and nothing spills, and

@@ -23,7 +23,7 @@
 //           Tu is applied to the residual (no per-slice W = T K precompute).
 //           Value columns never interact (Eq. slices), which is what makes
 //           the 16-column tiling exact.
-//   Inference with bf16 operands and K >= 64 runs the look-ahead pair of
+//   Inference with bf16 operands, K >= 64 and E >= 4 runs the look-ahead pair of
 //   tla_la_fwd.hpp instead.
 #include "tla_common.hpp"
 #include "tla_internal.hpp"

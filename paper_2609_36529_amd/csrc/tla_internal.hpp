@@ -45,7 +45,8 @@ __device__ __forceinline__ int seq_len(const Shape& s, int b) {
 struct PrepBufs {
   float* coef;   // [ch][3][E][C]  a = k2*gamma, b = q2*gamma, c = k2*gamma^C/gamma
   float* gC;     // [ch][E4]       gamma^C (E4 = E rounded up to 4)
-  void* ops;     // [ch][op_tile_elems] operand tiles, see OpTiles
+  void* ops;     // [ch][op_tile_elems] operand tiles: OpTiles, or for the
+                 // look-ahead instances LaOps, which take no more room
   float* ninv;   // [ch][C][C]     (I + L)^{-1} in fp32 (GDN training forward), or NULL
   int bwd_tiles; // training forward: also write Q^T (read only by the backward)
 };
@@ -84,7 +85,9 @@ struct SavedBufs {
 
 struct BwdBufs {
   void* dSck;    // [ch][E][V/16][K][16] state gradients at chunk ends, operand type
-                 // (rows in the same key order as Sck)
+                 // (rows in the same key order as Sck); from the 8-column reverse
+                 // recurrence (rec_halves) each 16 x 16 block as two 16 x 8 halves,
+                 // one after the other
   void* dSck_lo; // bf16 operands with a final-state gradient: the low bf16 part of
                  // the same gradients (dSck holds the rounded high part); else NULL
   float* dU;     // [ch][C][V]
@@ -106,8 +109,9 @@ inline int round4(int x) { return (x + 3) & ~3; }
 hipError_t launch_prep(const Shape& s, const FwdIn& in, const PrepBufs& p, hipStream_t st);
 hipError_t launch_fwd(const Shape& s, const FwdIn& in, const PrepBufs& p, void* o,
                       float* s_final, const SavedBufs* saved, hipStream_t st);
-// The look-ahead instances (inference, bf16 operands, K >= 64): prep and forward.
-bool la_instance(int K, int C, int E, bool bf16);
+// The look-ahead instances (inference, bf16 operands, K >= 64, E >= 4): prep and
+// forward.  Their prep writes the tiles of LaOps (tla_la.hpp) into PrepBufs::ops.
+bool la_instance(const Shape& s);
 hipError_t launch_prep_la(const Shape& s, const FwdIn& in, const PrepBufs& p, hipStream_t st);
 hipError_t launch_fwd_la(const Shape& s, const FwdIn& in, const PrepBufs& p, void* o,
                          float* s_final, hipStream_t st);

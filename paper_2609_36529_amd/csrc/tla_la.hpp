@@ -1,5 +1,5 @@
-// Look-ahead recurrences (bf16 operands, K >= 64): the tiles that their prep
-// kernel writes and which instances use them.
+// Look-ahead recurrences (inference, bf16 operands, K >= 64, E >= 4): the tiles
+// that their prep kernel writes.
 //
 // The chunk recurrence of Eq. joint-chunk has a serial chain per chunk:
 // W_c = sum_e diag(a_e) K_c S_c, then U_c = Tu (V - W_c), then the state
@@ -63,19 +63,6 @@ __device__ __forceinline__ bf16x8 join8(bf16x4 a, bf16x4 b) {
 __device__ __forceinline__ bf16x8 half_op(const f32x16& x, int k) {
   return join8(cvt_frag<bf16_t>(f32x4{x[8 * k], x[8 * k + 1], x[8 * k + 2], x[8 * k + 3]}),
                cvt_frag<bf16_t>(f32x4{x[8 * k + 4], x[8 * k + 5], x[8 * k + 6], x[8 * k + 7]}));
-}
-// Sum over the two 16-lane rows of each lane half: lo and hi are eight values
-// a lane brings (rows 8 hf + 0..3 and + 4..7); the even row keeps the sums of
-// lo, the odd row those of hi, i.e. lane group g rows 4 g + j (gfx950 exchange
-// of the odd rows of the first operand with the even rows of the second).
-__device__ __forceinline__ f32x4 row_pair_sum(f32x4 lo, f32x4 hi) {
-  f32x4 r;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(lo[j]), __float_as_uint(hi[j]), false, false);
-    r[j] = __uint_as_float(x[0]) + __uint_as_float(x[1]);
-  }
-  return r;
 }
 // One 1 KiB piece of a linear copy into shared memory (off = 16 lane).
 __device__ __forceinline__ void dma_kib(void* dst, const void* src, uint32_t off) {

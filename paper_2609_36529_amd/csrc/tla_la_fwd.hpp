@@ -1,7 +1,8 @@
 // Look-ahead forward of chunkwise triadic linear attention on gfx950 (bf16
-// operands, K >= 64): the prep kernel with the cross-chunk tiles, and the
+// operands, K >= 64, E >= 4): the prep kernel with the cross-chunk tiles, and the
 // recurrent forward.  See tla_la.hpp for the algebra.
-// (Compiled as part of tla_fwd.hip.)
+// Part of tla_fwd.hip, which alone includes it: one translation unit, and so one
+// code object, for the training and the inference forward.
 #pragma once
 #include "tla_la.hpp"
 
@@ -353,10 +354,12 @@ __global__ __launch_bounds__(la_prep_waves<E>() * 64, E <= 8 ? 4 : 2) void k_pre
 // without its memory operations: bound by the row waves' pass and the shared
 // memory's and the address units' throughput, not by the matrix cores.
 //
-// Every LA_SYNC-th chunk forms its W from its own start state instead (two
+// GDN: every LA_SYNC-th chunk forms its W from its own start state instead (two
 // more barriers): a sequence cut there and resumed from the handed-on fp32
 // state then repeats the uncut one bit for bit (elsewhere the two differ by
-// where the state's bf16 operand copy was rounded).
+// where the state's bf16 operand copy was rounded: 4e-5 of the outputs at E = 8,
+// cut at 512 of 812 tokens).  sGLA, whose U needs no state, repeats it at every
+// chunk boundary.
 constexpr int LA_SYNC = 16;
 
 template <int KD, int C, int E, bool PK>
@@ -815,6 +818,7 @@ static hipError_t fwd_la(const Shape& s, const FwdIn& in, const PrepBufs& p, voi
   }
 }
 
+// The instances, in one list: fields of s, CALL(K, C, E).
 #define TLA_LA_FOR_EACH(CALL)                                \
   if (s.K == 64 && s.C == 32 && s.E == 8) return CALL(64, 32, 8);    \
   if (s.K == 64 && s.C == 64 && s.E == 16) return CALL(64, 64, 16);  \
@@ -823,9 +827,12 @@ static hipError_t fwd_la(const Shape& s, const FwdIn& in, const PrepBufs& p, voi
   if (s.K == 128 && s.C == 64 && s.E == 16) return CALL(128, 64, 16); \
   if (s.K == 128 && s.C == 32 && s.E == 8) return CALL(128, 32, 8);
 
-bool la_instance(int K, int C, int E, bool bf16) {
-  return bf16 && ((K == 64 && C == 32 && E == 8) || (K == 64 && C == 64 && E == 16) ||
-                  (K == 128 && C == 64 && (E == 4 || E == 8 || E == 16)) || (K == 128 && C == 32 && E == 8));
+bool la_instance(const Shape& s) {
+  if (!s.in_bf16) return false;
+#define CALL_I(KD_, C_, E_) true
+  TLA_LA_FOR_EACH(CALL_I)
+#undef CALL_I
+  return false;
 }
 
 hipError_t launch_prep_la(const Shape& s, const FwdIn& in, const PrepBufs& p, hipStream_t st) {
