@@ -33,7 +33,9 @@
  *  - The caller owns every buffer.  The library allocates nothing, keeps no
  *    per-call state and never synchronises: work is enqueued on `stream`
  *    (a hipStream_t; NULL = the default stream) in a fixed order, so results
- *    are bitwise reproducible (no floating-point atomics anywhere).
+ *    are bitwise reproducible (no floating-point atomics anywhere).  What
+ *    tla_fwd and tla_bwd give for a sequence does not depend on the other
+ *    sequences of the call, batched or packed, to the bit.
  *  - Arguments are validated on the host before anything is enqueued; on
  *    error nothing is launched and a TLA_E_* code is returned
  *    (tla_last_error() then describes it).  TLA_E_DEVICE reports a failed
@@ -116,6 +118,15 @@ size_t tla_saved_bytes(const tla_desc* desc);
  *            backward consumes (training mode).
  *   ws     : device workspace of at least tla_workspace_bytes(desc, FWD);
  *            unused (may be NULL) when saved is given.
+ * A sequence may be cut at any position and continued from s_final.  Cut at a
+ * multiple of the chunk it repeats the uncut call bit for bit, with one
+ * exception: inference (saved = NULL) of TLA_GDN with bf16 operands, K >= 64
+ * and E >= 4 does so at multiples of 16 chunks.  At the chunk boundaries between,
+ * the first chunk after the cut takes the bf16 operands of its own start state
+ * where the uncut call takes those of the chunk before (at most 2^-8 apart,
+ * relative in the 2-norm; 4e-5 measured).  For the same instances (TLA_SGLA
+ * too) the inference and the training forward are different kernels, whose
+ * results agree to the rounding of the bf16 operands, not to the bit.
  */
 int tla_fwd(const tla_desc* desc, const void* q, const void* k, const void* v,
             const void* q2, const void* k2, const float* g, const float* beta,

@@ -119,21 +119,31 @@ def test_resume_at_sync(C):
 
 
 @pytest.mark.parametrize("variant", [0, 1])
-@pytest.mark.parametrize("E", [8, 16])
-def test_resume_elsewhere(variant, E):
-    """Cut at another chunk boundary (8 chunks of 64): sGLA, whose U needs no
-    state, repeats the uncut sequence bit for bit; GDN forms the W of the first
-    chunk from the bf16 operands of another state (that chunk's own start instead
-    of the one before), each element of which is within 2^-9 of the fp32 state:
+@pytest.mark.parametrize("path,E", [("inference", 8), ("inference", 16), ("training", 8), ("training", 16),
+                                    ("f32", 8)])
+def test_resume_elsewhere(variant, path, E):
+    """Cut at another chunk boundary (8 chunks of 64) a sequence repeats the uncut
+    one bit for bit, but for the GDN look-ahead forward: it forms the W of the first
+    chunk from the bf16 operands of another state (that chunk's own start instead of
+    the one before), each element of which is within 2^-9 of the fp32 state:
     operands at most 2^-8 apart, and so the results in the 2-norm (measured 4e-5)."""
     C, cut = 64, 512
-    inp = _inputs(variant, 1, cut + 300, 4, 128, 128, E, C)
-    o, sf = _fwd(variant, inp, C)
-    parts = [{k: (v if v is None or k == "s0" else v[:, sl].contiguous()) for k, v in inp.items()}
-             for sl in (slice(0, cut), slice(cut, None))]
-    _, mid = _fwd(variant, parts[0], C)
-    o2, sf2 = _fwd(variant, parts[1], C, s0=mid)
+    cfg = synth.Config("la", variant, 1, cut + 300, 4, 128, 128, E, C, "f32" if path == "f32" else "bf16",
+                       "softplus16", variant == 1, 0.02, 11)
+    inp = synth.make_inputs(cfg)
+
+    def run(sl, s0):
+        d = [None if inp[n] is None else inp[n][:, sl].contiguous().to("cuda")
+             for n in ("q", "k", "v", "q2", "k2", "g", "beta")]
+        o, sf, _ = tla.fwd(variant, *d, s0, chunk=C, out_dtype=torch.float32, training=path == "training")
+        torch.cuda.synchronize()
+        return o, sf
+
+    s0 = inp["s0"].to("cuda")
+    o, sf = run(slice(None), s0)
+    _, mid = run(slice(0, cut), s0)
+    o2, sf2 = run(slice(cut, None), mid)
     for x, y in ((o[:, cut:], o2), (sf, sf2)):
         d = ((x.double() - y.double()).norm() / x.double().norm()).item()
-        print(f"{variant=} {E=}: {d:.2e}", flush=True)
-        assert d <= (2.0 ** -8 if variant == 1 else 0.0)
+        print(f"{variant=} {path} {E=}: {d:.2e}", flush=True)
+        assert d <= (2.0 ** -8 if variant == 1 and path == "inference" else 0.0)
