@@ -349,10 +349,13 @@ __global__ __launch_bounds__(la_prep_waves<E>() * 64, E <= 8 ? 4 : 2) void k_pre
 // 180 / 155 us; K128 E8 B64 H16 T64 292 / 313 / 261 us).
 //
 // Measured (kernel alone, MI355X, before / after: the kernel whose W waits for
-// the update): GDN B1 H16 T65536 E16 3.85 / 2.90 ms, GDN B1 H16 T777 E8 58 /
-// 36 us, sGLA B4 H8 T4096 E8 177 / 124 us.  A GDN step takes 6.8 k cycles, 5.2 k
-// without its memory operations: bound by the row waves' pass and the shared
-// memory's and the address units' throughput, not by the matrix cores.
+// the update): GDN B1 H16 T65536 E16 3.85 / 2.95 ms, GDN B1 H16 T777 E8 58 /
+// 36 us, sGLA B4 H8 T4096 E8 177 / 124-129 us.  A GDN step takes 6.8 k cycles,
+// 5.2 k without its memory operations.  Counters (GDN B4 H8 T4096 E8, 180 us; in
+// brackets B1 H16 T65536 E16): matrix cores busy 34% (36%) of the cycles, shared
+// memory active 33% (40%) with 0.19 (0.27) conflict cycles each, waves waiting
+// 25% (25%) of their time: bound by the chain of a step through its two barriers,
+// not by one unit.
 //
 // GDN: every LA_SYNC-th chunk forms its W from its own start state instead (two
 // more barriers): a sequence cut there and resumed from the handed-on fp32
