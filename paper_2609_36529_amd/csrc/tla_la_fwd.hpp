@@ -428,16 +428,6 @@ __global__ __launch_bounds__(512, C == 32 ? 4 : 2) void k_fwd_la(Shape s, FwdIn 
 #pragma unroll
         for (int k = 0; k < 2; ++k) sm.sop[un][2 * (kt0 + i) + k][l] = half_op(S[i], k);
     };
-#pragma unroll
-    for (int i = 0; i < NKT; ++i) {
-      S[i] = zero16();
-      if (in.s0) {
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) S[i][4 * a + j] = state_ptr(in.s0, i, a)[(size_t)j * V];
-      }
-    }
     const T* Vg = (const T*)in.v + (tok0 * s.H + h) * (size_t)V + v0;
     const size_t vrs = (size_t)s.H * V;
     const bool sbeta = !GDN && in.beta != nullptr;
@@ -478,11 +468,32 @@ __global__ __launch_bounds__(512, C == 32 ? 4 : 2) void k_fwd_la(Shape s, FwdIn 
           p.coef + (ch0 + c) * 3 * E * C + E * C);
       if (w == 3 && l < E4) lds_dma<4>(uniform_ptr(p.gC + (ch0 + c) * E4), 4 * l, lds_addr(&sm.gC[c & 1][0]));
     };
-    if (nc > 0) {
-      put_sop();
+    // The first copies go out before the initial state is read (one memory latency
+    // for both) where that is faster.  After / before, whole calls: GDN K64 E16 B64
+    // H16 T64 217 / 211 us, B1 H8 T4096 152 / 150, the forward kernel of K128 E16
+    // B64 H16 T64 with an initial state 726 / 712; but sGLA K128 E8 B64 H16 T64 224 /
+    // 238 and GDN at C = 32 (K128 E8 B64 H16 T64) 231 / 240.
+    constexpr bool COPIES_FIRST = GDN && NT == 4;
+    auto copies = [&]() {
+      if (nc == 0) return;
       dma_a(0);
       dma_k(0);
       if (nc > 1) dma_a(1);
+    };
+    if constexpr (COPIES_FIRST) copies();
+#pragma unroll
+    for (int i = 0; i < NKT; ++i) {
+      S[i] = zero16();
+      if (in.s0) {
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) S[i][4 * a + j] = state_ptr(in.s0, i, a)[(size_t)j * V];
+      }
+    }
+    if (nc > 0) {
+      put_sop();
+      if constexpr (!COPIES_FIRST) copies();
       wait_vmcnt<0>();
     }
     for (int c = 0; c < nc; ++c) {
